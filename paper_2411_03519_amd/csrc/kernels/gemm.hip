@@ -261,17 +261,14 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restri
 }
 
 // ---------------------------------------------------------------------------
-// Tiled GEMM (prefill chunks, large decode batches), bound by the matrix
-// cores.  Block tile 256 (n, rows of W) x 256 (m, activation rows); 8 waves in
-// 4 x 2 (two per SIMD), each 64 x 128 = 2 x 4 tiles of
+// Tiled GEMM for batches of 65 to a few hundred rows.  Waves of TN x TM tiles of
 // v_mfma_f32_32x32x16_bf16 (A = W rows, B = activation rows).  Lane l
 // supplies A[l%32][8(l/32) .. +7] and B[8(l/32) .. +7][l%32] and receives D
 // rows 8q + 4(l/32) + i (q = 0..3, i = 0..3) of column l%32: four consecutive
 // output features of one activation row per q.
 //
 // Operands reach LDS by direct loads (global_load_lds_dwordx4: each lane's 16
-// bytes land at LDS base + 16 * lane), through a ring of NS stages (Big: 5 of
-// 32-wide k); the loads of the later stages are in flight while one is
+// bytes land at LDS base + 16 * lane), through a ring of NS stages; the loads of the later stages are in flight while one is
 // consumed, with no staging registers.  In LDS the weights keep their packed 16 x 32 tiles in
 // lane order, so every MFMA operand read by 16 lanes is 256 contiguous bytes,
 // free of bank conflicts.  Activations in 32-wide k stages are gathered into
@@ -286,8 +283,8 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restri
 // kt + 1, after the barrier that every wave passes only once done reading it.
 // ---------------------------------------------------------------------------
 // Tile shapes: WN x WM waves, each TN x TM tiles of 32 x 32, NS stages of
-// KT 32-wide k tiles in the LDS ring.  Big: 256 x 256 blocks for long prefill
-// chunks.  Mid: 128 x 128 blocks for batches of 65 to a few hundred rows: 8
+// KT 32-wide k tiles in the LDS ring.
+// Mid: 128 x 128 blocks for batches of 65 to a few hundred rows: 8
 // waves of 64 x 32 (two per SIMD) and a ring of 4 stages of 64-wide k (128
 // KiB).  At these sizes the k loop itself was the cost: with every global
 // load skipped the former Mid tile (4 waves of 64 x 64, 5 stages of 32-wide
@@ -302,6 +299,7 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restri
 template <int WN_, int WM_, int TN_, int TM_, int NS_, int KT_ = 1>
 struct TileShape {
   static constexpr int WN = WN_, WM = WM_, TN = TN_, TM = TM_, NS = NS_, KT = KT_;
+  static constexpr bool kQuad = false;
   static constexpr int WAVES = WN * WM, NTH = WAVES * 64;
   static constexpr int BN = WN * TN * 32, BM = WM * TM * 32;  // block tile
   static constexpr int WT = BN / 16, XT = BM / 16;            // 16 x 32 tiles per k tile
@@ -310,7 +308,6 @@ struct TileShape {
   static_assert(NS >= 3, "the pipeline keeps a stage in use, one landed and loads in flight");
   static_assert(KT == 1 || KT == 2 || KT == 4, "stages of 32, 64 or 128 k");
 };
-using BigTile = TileShape<4, 2, 2, 4, 5>;
 using MidTile = TileShape<2, 4, 2, 1, 4, 2>;
 // Wide: 256 rows of W x 128 activation rows, 8 waves of 64 x 64, 5 stages
 // (120 KiB), for wide products at up to 256 rows when 128 x 128 tiles would be
@@ -345,12 +342,13 @@ __device__ __forceinline__ void wait_later_stages(int later) {
   }
 }
 
-// Grouped tile order: tiles in launch order sweep groups of kGroupM m-tiles,
-// m fastest within a group, so the ~256 blocks in flight cover a compact
-// patch of tiles and share their W and X tiles through the caches.
+// Grouped tile order: consecutive tiles sweep groups of kGroupM m-tiles, m
+// fastest within a group, so that the blocks in flight cover a compact patch of
+// tiles and share their W and X tiles through the caches (256 x 256 tiles: 32
+// consecutive ones, the CUs of one XCD, cover 4 x 8).
 template <class S>
 __host__ __device__ __forceinline__ void tile_origin(int t, int M, int N, int& m0, int& n0) {
-  constexpr int kGroupM = 16;
+  constexpr int kGroupM = S::BM * S::BN < 256 * 256 ? 16 : 4;
   const int mt = (M + S::BM - 1) / S::BM, nt = (N + S::BN - 1) / S::BN;
   const int group = t / (kGroupM * nt);
   const int first_m = group * kGroupM;
@@ -365,8 +363,7 @@ __host__ __device__ __forceinline__ void tile_origin(int t, int M, int N, int& m
 // every XCD gets a contiguous run of the work list: in tile_origin order the
 // row tiles that read the same W columns are neighbours, so they run on one
 // XCD and share its L2 instead of each fetching W through the fabric.  In the
-// model (agent trace, 8B) this gained 2.5%; for prefill-sized 256 x 256 grids
-// it cost 1% and is not applied there.
+// model (agent trace, 8B) this gained 2.5%.
 __device__ __forceinline__ int xcd_contiguous(int b, int total) {
   constexpr int kXcds = 8;
   const int q = total / kXcds, r = total % kXcds, x = b % kXcds, s = b / kXcds;
@@ -375,8 +372,7 @@ __device__ __forceinline__ int xcd_contiguous(int b, int total) {
 
 // Work of one workgroup.  Without a tail split the grid's tiles x k slices
 // (slice-major list, tiles in tile_origin order) are spread over the XCDs by
-// xcd_contiguous (256 x 256 tiles: only up to kSplitMaxRows rows; above, the
-// list in grid order).  With one (tail_split = S > 1), workgroups x <
+// xcd_contiguous.  With one (tail_split = S > 1), workgroups x <
 // tail_first take tile x over all of K, and the last tiles, which would leave
 // most CUs idle in the final round, are cut into S k slices each: workgroup
 // tail_first + u takes slice u % S of tile tail_first + u / S and stores its
@@ -386,7 +382,7 @@ __global__ __launch_bounds__(S::NTH) void gemm_tiled_kernel(const uint16_t* __re
                                                             const uint16_t* __restrict__ W, int Kp, int M, int N,
                                                             float* __restrict__ outf, uint16_t* __restrict__ outb,
                                                             int ldo, float* __restrict__ part, int tail_first,
-                                                            int tail_split, RopeKV rk) {
+                                                            int tail_split) {
   constexpr int WM = S::WM, TN = S::TN, TM = S::TM, NS = S::NS, LPW = S::LPW, KT = S::KT;
   __shared__ uint4 wring[NS][KT * S::WT * 64];  // per stage and k tile: WT tiles of 16 x 32 (1 KiB each)
   __shared__ uint4 xring[NS][KT * S::XT * 64];
@@ -402,7 +398,7 @@ __global__ __launch_bounds__(S::NTH) void gemm_tiled_kernel(const uint16_t* __re
     tile = tail_first + unit / tail_split;
     KS = tail_split;
     slice = unit % tail_split;
-  } else if (tail_split == 1 && (S::BM * S::BN < 256 * 256 || M <= kSplitMaxRows)) {
+  } else if (tail_split == 1) {
     const int i = xcd_contiguous(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     slice = i / gridDim.x;
     tile = i % gridDim.x;
@@ -552,31 +548,6 @@ __global__ __launch_bounds__(S::NTH) void gemm_tiled_kernel(const uint16_t* __re
   // group of activation rows, then adds and stores them (one round trip per
   // group rather than per value); the scheduling barrier keeps the compiler
   // from hoisting every group's loads at once.
-  if constexpr (EPI == kEpiRopeKV) {
-    // (launched without k slices) each 16-row block of a 32-row tile holds 8
-    // dims of a head's first half, then the matching 8 of its second half in
-    // the rotate-half interleave: the lane's rows 8q + 4(l/32) + i of q = 0, 2
-    // pair with those of q = 1, 3 in the same lane
-#pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      const int m = m0 + wm * TM * 32 + j * 32 + lr;
-      if (m >= M) continue;
-#pragma unroll
-      for (int i = 0; i < TN; ++i) {
-        const int nb = n0 + wn * TN * 32 + i * 32;
-        if (nb >= N) continue;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int r0 = nb + 16 * u;  // first W row of the 16-row block
-          const f32x4 a{acc[i][j][8 * u], acc[i][j][8 * u + 1], acc[i][j][8 * u + 2], acc[i][j][8 * u + 3]};
-          const f32x4 b{acc[i][j][8 * u + 4], acc[i][j][8 * u + 5], acc[i][j][8 * u + 6], acc[i][j][8 * u + 7]};
-          store_rope_kv(a, b, m, r0 / rk.hd, 8 * ((r0 % rk.hd) / 16) + 4 * lh, rk);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-    return;
-  }
   const bool raw = KS > 1;
   float* const pout = unit >= 0 ? part + static_cast<size_t>(unit) * S::BM * S::BN
                       : raw     ? part + static_cast<size_t>(slice) * M * N
@@ -645,6 +616,383 @@ __global__ __launch_bounds__(S::NTH) void gemm_tiled_kernel(const uint16_t* __re
         }
       }
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Tiled GEMM of 4 waves, one per SIMD (2 x 2, each 16 TN rows of W x 16 TM
+// activation rows of v_mfma_f32_16x16x32_bf16), for prefill chunks.
+//
+// What bounds it: with random operands the chip runs against its power limit,
+// so the energy per flop counts as much as the stalls.
+//  - 16x16x32 instead of 32x32x16 MFMAs: the accumulators are read and written
+//    half as often (a loop of nothing but MFMAs on random data: 2125 against
+//    1862 TFLOP/s).
+//  - 128 x 128 per wave: 128 KiB of LDS reads per 64-wide k step of a 256 x 256
+//    tile, against 192 KiB for 8 waves of 64 x 128.
+//  - a wave alone on its SIMD has nobody to cover its stalls: each memory
+//    instruction rides behind an MFMA, fragments are read one chunk ahead, and
+//    operands are requested two to three chunks ahead.
+// Ring: 4 chunks of 32-wide k for W (operand order, copied as is), 3 stages of
+// 64-wide k for X (whole cache lines; row r keeps its 16-byte chunk c in slot
+// c ^ r % 8, which keeps the fragment reads free of bank conflicts); for
+// 256 x 256 tiles all 160 KiB.  Chunk c: its MFMAs, the fragments of c + 1, the
+// requests of W chunk c + 4 into the slot just freed and of half an X stage,
+// then a barrier (chunk c + 2 has landed, c + 1 is in registers everywhere).
+// Measured, 8 waves of 64 x 128 with 32x32x16 MFMAs before: 8B gate/up at
+// M = 8192 1634 -> 1352 us (1424 TFLOP/s), down 822 -> 649 us (1482), QKV 358
+// -> 289 us, 70B gate/up 6281 -> 5062 us (1520).
+// ---------------------------------------------------------------------------
+template <int TN_, int TM_>
+struct QuadShape {
+  static constexpr bool kQuad = true;
+  static constexpr int TN = TN_, TM = TM_;  // 16 x 16 tiles per wave
+  static constexpr int NTH = 256, BN = 32 * TN, BM = 32 * TM;
+  static constexpr int WS = 4, XS = 3;
+  static constexpr int LW = TN / 2, LX = TM / 2;  // direct loads per wave and chunk
+  static constexpr int kLds = WS * BN * 4 + XS * BM * 8;  // 16-byte units
+  static_assert(TN % 4 == 0 && TM % 4 == 0, "the waves share each chunk evenly");
+};
+
+using BigTile = QuadShape<8, 8>;
+
+// 16 bytes per lane from base + off (base wave-uniform) into LDS
+__device__ __forceinline__ void lds_load16s(const void* base, uint32_t off, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base)
+               : "memory", "m0");
+}
+
+// c += a . b with the accumulator held in place in AGPRs: 64 of these fill the
+// AGPR half of the register file, and left to itself the compiler's register
+// allocation moves them about inside the loop (430 moves per 128 MFMAs).  The
+// compiler does not see these MFMAs' hazards: an accumulator is touched once
+// per chunk, and no chunk ends without drained_barrier, behind which the
+// accumulators may be read (tests/test_gemm_accumulators.py checks the code).
+__device__ __forceinline__ void mfma16_acc(f32x4& c, uint4 a, uint4 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(as_bf16x8(a)), "v"(as_bf16x8(b)));
+}
+// The same with a direct load into LDS bytes lds_base + INC + 16 * lane behind
+// it; the MFMA is the wait state between the M0 write and the load.
+template <int INC>
+__device__ __forceinline__ void mfma16_acc_load(f32x4& c, uint4 a, uint4 b, const void* base, uint32_t off,
+                                                uint32_t lds_base) {
+  asm volatile(
+      "s_add_u32 m0, %3, %4\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\tglobal_load_lds_dwordx4 %5, %6"
+      : "+a"(c)
+      : "v"(as_bf16x8(a)), "v"(as_bf16x8(b)), "s"(lds_base), "n"(INC), "v"(off), "s"(base)
+      : "memory", "m0", "scc");
+}
+// All of the wave's LDS reads are in, its last MFMA has left its accumulator
+// readable (8 wait states), and every other wave is as far.
+__device__ __forceinline__ void drained_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_nop 7\n\ts_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Epilogues go through the wave's share of LDS, 32 activation rows at a time,
+// so that global accesses cover whole cache lines (the accumulators hold 4
+// columns of 16 rows each).  Row r keeps its 16-byte chunk c in slot c ^ r.
+//
+// fp32: 2 or 4 whole rows of the wave's columns per access; the residual of
+// the next 32 rows is loaded meanwhile.
+template <class S, int EPI>
+__device__ __forceinline__ void quad_epilogue_f32(const f32x4 (&acc)[S::TN][S::TM], uint4* buf, int mw, int nw, int m0,
+                                                  int n0, int lane, int M, int N, int KS, int slice, int unit,
+                                                  float* __restrict__ outf, int ldo, float* __restrict__ part) {
+  constexpr int TN = S::TN, TM = S::TM, CH = 4 * TN;  // 16-byte chunks per row
+  constexpr int RPI = 64 / CH, NI = 32 / RPI;         // rows per access, accesses per 32 rows
+  const int r16 = lane & 15, g = lane >> 4;
+  const int col = lane % CH, sub = lane / CH;
+  const bool raw = KS > 1;
+  float* out = outf;
+  int ld = ldo, mb = mw, nb = nw + 4 * col;
+  const bool nok = nb < N;
+  const int mok = M - mw;  // rows of the wave's tile
+  nb = min(nb, N - 4);
+  if (unit >= 0) {
+    out = part + static_cast<size_t>(unit) * S::BM * S::BN;
+    ld = S::BN;
+    mb -= m0;
+    nb -= n0;
+  } else if (raw) {
+    out = part + static_cast<size_t>(slice) * M * N;
+    ld = N;
+  }
+  float* const base = out + static_cast<size_t>(mb) * ld + nb;
+  const bool add = EPI == kEpiAddF32 && !raw;
+  float4 res[2][NI];
+  auto load_res = [&](int q) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < NI; ++t)
+      res[q & 1][t] =
+          *reinterpret_cast<const float4*>(base + static_cast<ptrdiff_t>(min(32 * q + RPI * t + sub, mok - 1)) * ld);
+  };
+  if (EPI == kEpiAddF32) {
+    if (add) load_res(0);
+  }
+#pragma unroll
+  for (int q = 0; q < TM / 2; ++q) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int i = 0; i < TN; ++i) {
+        const int r = 16 * j + r16;
+        buf[r * CH + ((4 * i + g) ^ (r % CH))] = __builtin_bit_cast(uint4, acc[i][2 * q + j]);
+      }
+    if (EPI == kEpiAddF32) {
+      if (add && q + 1 < TM / 2) load_res(q + 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < NI; ++t) {
+      const int r = RPI * t + sub;
+      float4 v = __builtin_bit_cast(float4, buf[r * CH + (col ^ (r % CH))]);
+      if (EPI == kEpiAddF32) {
+        if (add) {
+          v.x += res[q & 1][t].x;
+          v.y += res[q & 1][t].y;
+          v.z += res[q & 1][t].z;
+          v.w += res[q & 1][t].w;
+        }
+      }
+      if (nok && 32 * q + r < mok) *reinterpret_cast<float4*>(base + static_cast<size_t>(32 * q + r) * ld) = v;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The halves of two 16-row blocks of W brought together: lanes 0-31 get rows
+// 0-7 (lo) and the matching rows 8-15 (hi) of block x, lanes 32-63 of block y.
+__device__ __forceinline__ void pair_halves(f32x4 x, f32x4 y, f32x4& lo, f32x4& hi) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[r]), __float_as_uint(y[r]), false, false);
+    lo[r] = __uint_as_float(p[0]);
+    hi[r] = __uint_as_float(p[1]);
+  }
+}
+
+// SwiGLU: the wave's 8 TN outputs per row (16 TN bytes)
+template <class S>
+__device__ __forceinline__ void quad_epilogue_swiglu(const f32x4 (&acc)[S::TN][S::TM], uint4* buf, int mw, int nw,
+                                                     int lane, int M, int N, uint16_t* __restrict__ outb, int ldo) {
+  constexpr int TN = S::TN, TM = S::TM, CH = TN;  // 16-byte chunks per row
+  constexpr int RPI = 64 / CH, NI = 32 / RPI;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int col = lane % CH, sub = lane / CH;
+  uint2* const buf8 = reinterpret_cast<uint2*>(buf);
+  const bool nok = nw + 16 * col < N;
+#pragma unroll
+  for (int q = 0; q < TM / 2; ++q) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int i = 0; i < TN; i += 2) {
+        f32x4 gt, up;
+        pair_halves(acc[i][2 * q + j], acc[i + 1][2 * q + j], gt, up);
+        const int r = 16 * j + r16, c = i + (g >> 1);
+        uint2 o;
+        o.x = pack_bf16x2(silu_f32(gt[0]) * up[0], silu_f32(gt[1]) * up[1]);
+        o.y = pack_bf16x2(silu_f32(gt[2]) * up[2], silu_f32(gt[3]) * up[3]);
+        buf8[(r * CH + (c ^ (r % CH))) * 2 + (g & 1)] = o;
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < NI; ++t) {
+      const int r = RPI * t + sub, m = mw + 32 * q + r;
+      const uint4 v = buf[r * CH + (col ^ (r % CH))];
+      if (nok && m < M) {
+        uint2* p = reinterpret_cast<uint2*>(outb + static_cast<size_t>(m) * ldo + nw / 2 + 8 * col);
+        p[0] = make_uint2(v.x, v.y);  // (rows of the output are 8-byte aligned)
+        p[1] = make_uint2(v.z, v.w);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Work of one workgroup: as gemm_tiled_kernel, every XCD taking a contiguous
+// run of the work list.  In tile_origin order 32 consecutive tiles (one XCD's
+// CUs) cover 4 x 8 tiles, so an XCD's L2 fetches 12 operand tiles per k step;
+// the list in grid order made that 18 (8B gate/up at M = 8192 1506 -> 1479 us).
+template <class S, int EPI>
+__global__ __launch_bounds__(S::NTH, 1) void gemm_quad_kernel(const uint16_t* __restrict__ X, int ldx,
+                                                              const uint16_t* __restrict__ W, int Kp, int M, int N,
+                                                              float* __restrict__ outf, uint16_t* __restrict__ outb,
+                                                              int ldo, float* __restrict__ part, int tail_first,
+                                                              int tail_split, RopeKV rk) {
+  constexpr int TN = S::TN, TM = S::TM, WS = S::WS, XS = S::XS, LW = S::LW, LX = S::LX;
+  __shared__ uint4 lds[S::kLds];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wn = wave >> 1, wm = wave & 1;
+  const int r16 = lane & 15, g = lane >> 4;
+
+  int tile = blockIdx.x, KS = gridDim.y, slice = blockIdx.y, unit = -1;
+  if (tail_split > 1 && tile >= tail_first) {
+    unit = tile - tail_first;
+    tile = tail_first + unit / tail_split;
+    KS = tail_split;
+    slice = unit % tail_split;
+  } else if (tail_split > 1) {
+    tile = xcd_contiguous(tile, tail_first);
+  } else {
+    const int i = xcd_contiguous(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+    slice = i / gridDim.x;
+    tile = i % gridDim.x;
+  }
+  const int kspan = Kp / KS, k0 = slice * kspan;
+  const int nc = kspan / 32;  // chunks (a multiple of 4)
+  int m0, n0;
+  tile_origin<S>(tile, M, N, m0, n0);
+
+  // The wave's share of every W chunk (16-row tiles) and X stage (blocks of 8
+  // rows).  Rows past N or M re-read the last valid row: finite values whose
+  // products only reach outputs that are not stored.
+  const char* const wbase =
+      reinterpret_cast<const char*>(W + (static_cast<size_t>(n0 / 16) * (Kp / 32) + k0 / 32) * 512);
+  const char* const xbase = reinterpret_cast<const char*>(X + static_cast<size_t>(m0) * ldx + k0);
+  uint32_t woff[LW], xoff[2 * LX];
+#pragma unroll
+  for (int j = 0; j < LW; ++j) {
+    const int rt = min(LW * wave + j, N / 16 - 1 - n0 / 16);
+    woff[j] = static_cast<uint32_t>(rt) * (Kp / 32) * 1024 + lane * 16;
+  }
+#pragma unroll
+  for (int j = 0; j < 2 * LX; ++j) {
+    const int u = 2 * LX * wave + j;
+    const int row = min(8 * u + (lane >> 3), M - 1 - m0);
+    xoff[j] = (static_cast<uint32_t>(row) * ldx + 8 * ((lane & 7) ^ (lane >> 3))) * 2;
+  }
+  const uint32_t wlds = lds_address(lds) + wave * LW * 1024;
+  const uint32_t xlds = lds_address(lds + WS * S::BN * 4) + wave * LX * 2048;
+  constexpr uint32_t kWSlot = S::BN * 64, kXSlot = S::BM * 128;  // bytes of a W chunk, an X stage
+
+  f32x4 acc[TN][TM];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const uint32_t wfrag = wn * TN * 1024 + lane * 16;
+  const int xrow = wm * TM * 16 + r16;
+  const uint32_t xfrag = WS * kWSlot + (xrow >> 3) * 1024 + (xrow & 7) * 128 + 16 * (g ^ (xrow & 7));
+  const char* const ldsb = reinterpret_cast<const char*>(lds);
+  uint4 a[2][TN], b[2][TM];
+  // the u-th fragment, in order of first use, of the chunk (odd: second half of
+  // its stage) at ring offsets wo, xo
+  auto read_frag = [&](int u, int odd, uint32_t wo, uint32_t xo) __attribute__((always_inline)) {
+    if (u >= 1 && u <= TM) {
+      b[odd][u - 1] = *reinterpret_cast<const uint4*>(ldsb + ((xfrag ^ (64 * odd)) + xo) + (u - 1) * 2048);
+    } else {
+      const int i = u == 0 ? 0 : u - TM;
+      a[odd][i] = *reinterpret_cast<const uint4*>(ldsb + (wfrag + wo) + i * 1024);
+    }
+  };
+
+  auto load_w = [&](int c, int j) __attribute__((always_inline)) {
+    lds_load16s(wbase + c * 1024, woff[j], wlds + c * kWSlot + j * 1024);
+  };
+  auto load_x = [&](int s, int j) __attribute__((always_inline)) {
+    lds_load16s(xbase + min(s, nc / 2 - 1) * 128, xoff[j], xlds + s * kXSlot + j * 1024);
+  };
+#pragma unroll
+  for (int j = 0; j < LW; ++j) load_w(0, j);
+#pragma unroll
+  for (int j = 0; j < 2 * LX; ++j) load_x(0, j);
+#pragma unroll
+  for (int j = 0; j < LW; ++j) load_w(1, j);
+#pragma unroll
+  for (int j = 0; j < 2 * LX; ++j) load_x(1, j);
+#pragma unroll
+  for (int c = 2; c < 4; ++c)
+#pragma unroll
+    for (int j = 0; j < LW; ++j) load_w(c, j);
+#pragma unroll
+  for (int j = 0; j < LX; ++j) load_x(2, j);
+  wait_vmcnt<3 * LW + 3 * LX>();
+  lds_barrier();
+#pragma unroll
+  for (int u = 0; u < TN + TM; ++u) read_frag(u, 0, 0, 0);
+  wait_vmcnt<2 * LW + 3 * LX>();
+  drained_barrier();
+
+  // One chunk, in fragment set P = parity of the chunk: its MFMAs, the
+  // fragments of the next chunk (ring offsets wo, xo), the loads of a W chunk
+  // (from wsrc to ring offset wd) and of half an X stage (xsrc, xd); then the
+  // barrier behind which the chunk after the next has landed: the loads of the
+  // last two chunks, and the X half before them if that chunk continues its
+  // stage, are younger.  At most one memory instruction per MFMA: a burst of
+  // LDS reads would back up and hold the wave's next MFMA.
+  auto chunk = [&](auto par, uint32_t wo, uint32_t xo, const char* wsrc, uint32_t wd, const char* xsrc,
+                   uint32_t xd) __attribute__((always_inline)) {
+    constexpr int P = decltype(par)::value, NM = TN * TM;
+    static_assert(2 * (TN + TM) <= NM, "the fragment reads fit behind every other MFMA");
+    [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
+      (([&]() __attribute__((always_inline)) {
+         constexpr int i = U / TM, j = (i & 1) ? TM - 1 - U % TM : U % TM;
+         // the direct loads spread over the chunk, behind odd MFMAs; the reads behind the first even ones
+         constexpr int l0 = U * (LW + LX) / NM, l1 = (U + 1) * (LW + LX) / NM;
+         constexpr int l = (l0 * NM / (LW + LX) | 1) == U ? l0 : (l1 * NM / (LW + LX) | 1) == U ? l1 : LW + LX;
+         if constexpr (l < LW)
+           mfma16_acc_load<l * 1024>(acc[i][j], a[P][i], b[P][j], wsrc, woff[l], wd);
+         else if constexpr (l < LW + LX)
+           mfma16_acc_load<((P ? 0 : LX) + l - LW) * 1024>(acc[i][j], a[P][i], b[P][j], xsrc,
+                                                           xoff[(P ? 0 : LX) + l - LW], xd);
+         else
+           mfma16_acc(acc[i][j], a[P][i], b[P][j]);
+         if constexpr (U % 2 == 0 && U / 2 < TN + TM) read_frag(U / 2, P ^ 1, wo, xo);
+         __builtin_amdgcn_sched_barrier(0);
+       }()),
+       ...);
+    }(std::make_integer_sequence<int, NM>{});
+    wait_vmcnt<2 * LW + (P ? 3 : 2) * LX>();
+    drained_barrier();
+  };
+  // Requests past the last chunk re-read it into slots that are no longer
+  // needed (the caches hold it), and the last fragments read are never used:
+  // so every chunk is the same code and the same counts.
+  uint32_t wo = 0, x0 = 0, x1 = kXSlot, x2 = 2 * kXSlot;
+  for (int c = 0; c < nc; c += 2) {
+    const int s = c >> 1, last = nc - 1;
+    chunk(std::integral_constant<int, 0>{}, wo + kWSlot, x0, wbase + min(c + 4, last) * 1024, wlds + wo,
+          xbase + min(s + 2, last >> 1) * 128, xlds + x2);
+    chunk(std::integral_constant<int, 1>{}, wo ^ (2 * kWSlot), x1, wbase + min(c + 5, last) * 1024,
+          wlds + wo + kWSlot, xbase + min(s + 3, last >> 1) * 128, xlds + x0);
+    wo ^= 2 * kWSlot;
+    const uint32_t x = x0;
+    x0 = x1;
+    x1 = x2;
+    x2 = x;
+  }
+  wait_vmcnt<0>();
+  drained_barrier();
+  const int mw = m0 + wm * TM * 16, nw = n0 + wn * TN * 16;
+  uint4* const buf = lds + wave * (S::kLds / 4);
+  if constexpr (EPI == kEpiRopeKV) {  // launched without k slices
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+      const int m = mw + 16 * j + r16;
+#pragma unroll
+      for (int i = 0; i < TN; i += 2) {
+        // a 16-row block of W: 8 dims of a head's first half, then the
+        // matching 8 of its second half (rotate-half interleave)
+        f32x4 x, y;
+        pair_halves(acc[i][j], acc[i + 1][j], x, y);
+        const int r0 = nw + 16 * (i + (g >> 1));
+        if (m < M && r0 < N) store_rope_kv(x, y, m, r0 / rk.hd, 8 * ((r0 % rk.hd) / 16) + 4 * (g & 1), rk);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  } else if constexpr (EPI == kEpiSwiGLU) {
+    if (KS > 1)
+      quad_epilogue_f32<S, kEpiStoreF32>(acc, buf, mw, nw, m0, n0, lane, M, N, KS, slice, unit, outf, ldo, part);
+    else
+      quad_epilogue_swiglu<S>(acc, buf, mw, nw, lane, M, N, outb, ldo);
+  } else {
+    quad_epilogue_f32<S, EPI>(acc, buf, mw, nw, m0, n0, lane, M, N, KS, slice, unit, outf, ldo, part);
   }
 }
 
@@ -864,8 +1212,12 @@ static void launch_tiled(const uint16_t* X, int ldx, const uint16_t* W, int Kp, 
                          int tail_first = 0) {
   const int tiles = ((N + S::BN - 1) / S::BN) * ((M + S::BM - 1) / S::BM);
   const int blocks = tail_split > 1 ? tail_first + (tiles - tail_first) * tail_split : tiles;
-  launch_kernel((gemm_tiled_kernel<S, EPI>), dim3(blocks, ks), dim3(S::NTH), 0, s, X, ldx, W, Kp, M, N, outf, outb,
-                ldo, part, tail_first, tail_split, RopeKV{});
+  if constexpr (S::kQuad)
+    launch_kernel((gemm_quad_kernel<S, EPI>), dim3(blocks, ks), dim3(S::NTH), 0, s, X, ldx, W, Kp, M, N, outf, outb, ldo,
+                  part, tail_first, tail_split, RopeKV{});
+  else
+    launch_kernel((gemm_tiled_kernel<S, EPI>), dim3(blocks, ks), dim3(S::NTH), 0, s, X, ldx, W, Kp, M, N, outf, outb,
+                  ldo, part, tail_first, tail_split);
   if (tail_split > 1) {
     if constexpr (EPI == kEpiSwiGLU)
       launch_kernel((gemm_tail_fixup_swiglu_kernel<S>), dim3(tiles - tail_first, S::BM / (2048 / S::BN)),
@@ -934,7 +1286,7 @@ hipError_t launch_gemm_rope_kv(const uint16_t* X, int ldx, const uint16_t* W, in
     return hipErrorInvalidValue;
   if (M > kRopeKVMaxRows) {  // 256 x 256 tiles over all of K (no workspace: no split of the last round)
     const int tiles = ((N + BigTile::BN - 1) / BigTile::BN) * ((M + BigTile::BM - 1) / BigTile::BM);
-    launch_kernel((gemm_tiled_kernel<BigTile, kEpiRopeKV>), dim3(tiles, 1), dim3(BigTile::NTH), 0, s, X, ldx, W, Kp,
+    launch_kernel((gemm_quad_kernel<BigTile, kEpiRopeKV>), dim3(tiles, 1), dim3(BigTile::NTH), 0, s, X, ldx, W, Kp,
                   M, N, nullptr, nullptr, 0, nullptr, 0, 1, rk);
     return hipGetLastError();
   }
