@@ -261,86 +261,53 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restri
 }
 
 // ---------------------------------------------------------------------------
-// Tiled GEMM for batches of 65 to a few hundred rows.  Waves of TN x TM tiles of
-// v_mfma_f32_32x32x16_bf16 (A = W rows, B = activation rows).  Lane l
-// supplies A[l%32][8(l/32) .. +7] and B[8(l/32) .. +7][l%32] and receives D
-// rows 8q + 4(l/32) + i (q = 0..3, i = 0..3) of column l%32: four consecutive
-// output features of one activation row per q.
+// Tiled GEMM of 4 waves, one per SIMD (2 x 2, each 16 TN rows of W x 16 TM
+// activation rows of v_mfma_f32_16x16x32_bf16), for more than 64 rows.
 //
-// Operands reach LDS by direct loads (global_load_lds_dwordx4: each lane's 16
-// bytes land at LDS base + 16 * lane), through a ring of NS stages; the loads of the later stages are in flight while one is
-// consumed, with no staging registers.  In LDS the weights keep their packed 16 x 32 tiles in
-// lane order, so every MFMA operand read by 16 lanes is 256 contiguous bytes,
-// free of bank conflicts.  Activations in 32-wide k stages are gathered into
-// the same form (64 contiguous bytes of each of 16 rows per wave load); in
-// 64-wide k stages one wave load takes 8 whole rows of the stage (8 x 128
-// bytes, whole cache lines) into a 1 KiB block whose 16-byte chunks are
-// XOR-swizzled by row (act_chunk_slot), which keeps the operand reads free of
-// bank conflicts: 8 consecutive rows of one k chunk fall in 8 distinct
-// 16-byte slots of a 128-byte bank period (8B gate/up at M=128: 71.7 -> 66.3
-// us against half-line loads; agent trace 12.3-12.5k -> 12.8k tokens/s).
-// The stage consumed in step kt is refilled (with stage kt + NS - 1) in step
-// kt + 1, after the barrier that every wave passes only once done reading it.
+// What bounds it: for prefill chunks the chip's power limit, which it reaches
+// with random operands, so the energy per flop counts as much as the stalls;
+// for batches of up to about 256 rows the stream of W.
+//  - 16x16x32 instead of 32x32x16 MFMAs: the accumulators are read and written
+//    half as often (a loop of nothing but MFMAs on random data: 2125 against
+//    1862 TFLOP/s).
+//  - 128 x 128 per wave: 128 KiB of LDS reads per 64-wide k step of a 256 x 256
+//    tile, against 192 KiB for 8 waves of 64 x 128.
+//  - a wave alone on its SIMD has nobody to cover its stalls: each memory
+//    instruction rides behind an MFMA, fragments are read one chunk ahead, and
+//    operands are requested two to three chunks ahead.
+// Ring: 4 chunks of 32-wide k for W (operand order, copied as is), 3 stages of
+// 64-wide k for X (whole cache lines; row r keeps its 16-byte chunk c in slot
+// c ^ r % 8, which keeps the fragment reads free of bank conflicts); for
+// 256 x 256 tiles all 160 KiB.  Chunk c: its MFMAs, the fragments of c + 1, the
+// requests of W chunk c + 4 into the slot just freed and of half an X stage,
+// then a barrier (chunk c + 2 has landed, c + 1 is in registers everywhere).
+// Measured, 8 waves of 64 x 128 with 32x32x16 MFMAs before: 8B gate/up at
+// M = 8192 1634 -> 1352 us (1424 TFLOP/s), down 822 -> 649 us (1482), QKV 358
+// -> 289 us, 70B gate/up 6281 -> 5062 us (1520).
 // ---------------------------------------------------------------------------
-// Tile shapes: WN x WM waves, each TN x TM tiles of 32 x 32, NS stages of
-// KT 32-wide k tiles in the LDS ring.
-// Mid: 128 x 128 blocks for batches of 65 to a few hundred rows: 8
-// waves of 64 x 32 (two per SIMD) and a ring of 4 stages of 64-wide k (128
-// KiB).  At these sizes the k loop itself was the cost: with every global
-// load skipped the former Mid tile (4 waves of 64 x 64, 5 stages of 32-wide
-// k) still took 28 of its 62 us for the 8B gate/up at M=128, and the loads
-// added to that rather than hiding under it (ring depths 5, 8 and 9 all gave
-// the same time); stages twice as wide halve the barriers per unit of work
-// and the second wave per SIMD covers one wave's waits.  In the model: agent
-// trace 12.16k -> 12.56k tokens/s, fixed batch of 100 +5%, 70B at B=128
-// 2.55k -> 2.62k.
-// KT: 32-wide k tiles per stage (1, or 2 for 64-wide stages: half the
-// barriers per unit of work).
-template <int WN_, int WM_, int TN_, int TM_, int NS_, int KT_ = 1>
+template <int TN_, int TM_>
 struct TileShape {
-  static constexpr int WN = WN_, WM = WM_, TN = TN_, TM = TM_, NS = NS_, KT = KT_;
-  static constexpr bool kQuad = false;
-  static constexpr int WAVES = WN * WM, NTH = WAVES * 64;
-  static constexpr int BN = WN * TN * 32, BM = WM * TM * 32;  // block tile
-  static constexpr int WT = BN / 16, XT = BM / 16;            // 16 x 32 tiles per k tile
-  static constexpr int LPW = KT * (WT + XT) / WAVES;          // direct loads per wave per stage
-  static_assert((KT * (WT + XT)) % WAVES == 0, "the waves share the tiles of a stage evenly");
-  static_assert(NS >= 3, "the pipeline keeps a stage in use, one landed and loads in flight");
-  static_assert(KT == 1 || KT == 2 || KT == 4, "stages of 32, 64 or 128 k");
+  static constexpr int TN = TN_, TM = TM_;  // 16 x 16 tiles per wave
+  static constexpr int NTH = 256, BN = 32 * TN, BM = 32 * TM;
+  static constexpr int WS = 4, XS = 3;
+  static constexpr int LW = TN / 2, LX = TM / 2;  // direct loads per wave and chunk
+  static constexpr int kLds = WS * BN * 4 + XS * BM * 8;  // 16-byte units
+  static constexpr int OCC = kLds * 16 <= 80 * 1024 ? 2 : 1;  // workgroups per CU that its registers must allow
+  static_assert(TN % 4 == 0 && TM % 4 == 0, "the waves share each chunk evenly");
 };
-using MidTile = TileShape<2, 4, 2, 1, 4, 2>;
-// Wide: 256 rows of W x 128 activation rows, 8 waves of 64 x 64, 5 stages
-// (120 KiB), for wide products at up to 256 rows when 128 x 128 tiles would be
-// too many for one round: against 256 x 256 tiles it does no matrix work on
-// absent rows at M <= 128 (70B gate/up at M=128 in a probe: 202 against 267
-// us; the LM head at M=80: 225 against 268) and gives twice the workgroups at
-// M = 129..256 (8B gate/up at M=192: 78 against 91 us).
-using WideTile = TileShape<4, 2, 2, 2, 5>;
 
-__device__ __forceinline__ f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), c, 0, 0, 0);
-}
-
-// Slot of 16-byte chunk c of tile row `row` within that row's 128 bytes of a
-// swizzled activation block (64-wide k stages); the map is its own inverse,
-// so it also gives the chunk held in slot c.  The 8 rows of a block put one
-// chunk into 8 distinct slots of a 128-byte bank period, and rows of the next
-// block into the other half of a 256-byte one.
-__device__ __forceinline__ int act_chunk_slot(int c, int row) { return c ^ (row & 7) ^ ((row >> 3) & 1); }
-
-// wait until at most PER * min(later, MAXC) direct loads of this wave are outstanding
-template <int PER, int MAXC>
-__device__ __forceinline__ void wait_later_stages(int later) {
-  if constexpr (MAXC > 0) {
-    if (later >= MAXC) {
-      wait_vmcnt<PER * MAXC>();
-      return;
-    }
-    wait_later_stages<PER, MAXC - 1>(later);
-  } else {
-    wait_vmcnt<0>();
-  }
-}
+// Big: for prefill chunks.  Mid: for batches of 65 to a few hundred rows; 80
+// KiB of LDS, so two workgroups share a CU where there are enough.  Wide: for
+// wide products at up to 256 rows when 128 x 128 tiles would be too many for
+// one round: against 256 x 256 tiles it does no matrix work on absent rows at
+// M <= 128 and gives twice the workgroups at M = 129..256.  Against the former
+// 8-wave kernels of these tile sizes (32x32x16 MFMAs): 8B gate/up at M = 128 /
+// 200 / 256 50.8 / 75.2 / 83.1 -> 49.6 / 63.8 / 68.0 us, down at M = 200 45.3 ->
+// 42.2, O at M = 800 41.1 -> 36.6; 70B gate/up at M = 128 194 -> 172, QKV 56.5
+// -> 47.3; within 2% either way for the 70B down and QKV at M = 160..301.
+using BigTile = TileShape<8, 8>;
+using MidTile = TileShape<4, 4>;
+using WideTile = TileShape<8, 4>;
 
 // Grouped tile order: consecutive tiles sweep groups of kGroupM m-tiles, m
 // fastest within a group, so that the blocks in flight cover a compact patch of
@@ -369,292 +336,6 @@ __device__ __forceinline__ int xcd_contiguous(int b, int total) {
   const int q = total / kXcds, r = total % kXcds, x = b % kXcds, s = b / kXcds;
   return x * q + min(x, r) + s;
 }
-
-// Work of one workgroup.  Without a tail split the grid's tiles x k slices
-// (slice-major list, tiles in tile_origin order) are spread over the XCDs by
-// xcd_contiguous.  With one (tail_split = S > 1), workgroups x <
-// tail_first take tile x over all of K, and the last tiles, which would leave
-// most CUs idle in the final round, are cut into S k slices each: workgroup
-// tail_first + u takes slice u % S of tile tail_first + u / S and stores its
-// fp32 sums to part[u][BM][BN] for gemm_tail_fixup_kernel.
-template <class S, int EPI>
-__global__ __launch_bounds__(S::NTH) void gemm_tiled_kernel(const uint16_t* __restrict__ X, int ldx,
-                                                            const uint16_t* __restrict__ W, int Kp, int M, int N,
-                                                            float* __restrict__ outf, uint16_t* __restrict__ outb,
-                                                            int ldo, float* __restrict__ part, int tail_first,
-                                                            int tail_split) {
-  constexpr int WM = S::WM, TN = S::TN, TM = S::TM, NS = S::NS, LPW = S::LPW, KT = S::KT;
-  __shared__ uint4 wring[NS][KT * S::WT * 64];  // per stage and k tile: WT tiles of 16 x 32 (1 KiB each)
-  __shared__ uint4 xring[NS][KT * S::XT * 64];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wn = wave / WM, wm = wave % WM;  // the wave's (TN*32) x (TM*32) tile
-  const int lr = lane & 31, lh = lane >> 5;
-
-  // tile and k range (each slice a multiple of 128)
-  int tile = blockIdx.x, KS = gridDim.y, slice = blockIdx.y, unit = -1;
-  if (tail_split > 1 && tile >= tail_first) {
-    unit = tile - tail_first;
-    tile = tail_first + unit / tail_split;
-    KS = tail_split;
-    slice = unit % tail_split;
-  } else if (tail_split == 1) {
-    const int i = xcd_contiguous(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
-    slice = i / gridDim.x;
-    tile = i % gridDim.x;
-  }
-  const int kspan = Kp / KS, k0 = slice * kspan;
-  const int nk = kspan / (32 * KT);
-  int m0, n0;
-  tile_origin<S>(tile, M, N, m0, n0);
-
-  // Wave w loads tiles w*LPW .. w*LPW + LPW - 1 of the list [W tiles, X
-  // tiles] of every stage.  Rows past N or M re-read the last valid row:
-  // finite values whose products only reach outputs that are not stored.
-  const uint16_t* src[LPW];
-  uint32_t dst[LPW];
-  int src_step[LPW];       // elements per 32-wide k tile
-  uint32_t dst_step[LPW];  // bytes per stage of the operand's ring
-#pragma unroll
-  for (int j = 0; j < LPW; ++j) {
-    const int t = wave * LPW + j;  // [k tile 0: W tiles .. k tile KT-1: W tiles][the same for X]
-    if (t < KT * S::WT) {
-      const int kk = t / S::WT, wt = t % S::WT;
-      const int rt = min(n0 / 16 + wt, N / 16 - 1);
-      src[j] = W + (static_cast<size_t>(rt) * (Kp / 32) + k0 / 32 + kk) * 512 + lane * 8;
-      dst[j] = lds_address(&wring[0][0]) + t * 1024;
-      src_step[j] = 512 * KT;
-      dst_step[j] = KT * S::WT * 1024;
-    } else {
-      const int u = t - KT * S::WT, kk = u / S::XT, tx = u % S::XT;
-      if constexpr (KT == 2) {
-        // block u: rows 8u .. 8u+7 of the tile, all 64 k of the stage; lane l
-        // fills slot l % 8 of row 8u + l / 8
-        const int row = min(m0 + 8 * u + (lane >> 3), M - 1);
-        src[j] = X + static_cast<size_t>(row) * ldx + k0 + 8 * act_chunk_slot(lane & 7, 8 * u + (lane >> 3));
-        (void)kk;
-        (void)tx;
-      } else {
-        const int row = min(m0 + 16 * tx + (lane & 15), M - 1);
-        src[j] = X + static_cast<size_t>(row) * ldx + k0 + 32 * kk + 8 * (lane >> 4);
-      }
-      dst[j] = lds_address(&xring[0][0]) + u * 1024;
-      src_step[j] = 32 * KT;
-      dst_step[j] = KT * S::XT * 1024;
-    }
-  }
-  auto issue = [&](int kt) __attribute__((always_inline)) {
-    const uint32_t stage = kt % NS;
-#pragma unroll
-    for (int j = 0; j < LPW; ++j) lds_load16(src[j] + kt * src_step[j], dst[j] + stage * dst_step[j]);
-  };
-
-  f32x16 acc[TN][TM];
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int j = 0; j < TM; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // operand fragments of the 16-wide k half ks (0 .. 2 KT - 1) of stage kt
-  auto read_frags = [&](int kt, int ks, uint4 (&af)[TN], uint4 (&bf)[TM]) __attribute__((always_inline)) {
-    const uint4* ws = wring[kt % NS] + (ks >> 1) * S::WT * 64;
-    const int q = 16 * (2 * (ks & 1) + lh);  // chunk of the lane's 8 k values within a tile
-#pragma unroll
-    for (int i = 0; i < TN; ++i) {
-      const int row = wn * TN * 32 + i * 32 + lr;
-      af[i] = ws[(row >> 4) * 64 + (row & 15) + q];
-    }
-    if constexpr (KT == 2) {
-      const uint4* xs = xring[kt % NS];
-#pragma unroll
-      for (int j = 0; j < TM; ++j) {
-        const int row = wm * TM * 32 + j * 32 + lr;
-        bf[j] = xs[(row >> 3) * 64 + (row & 7) * 8 + act_chunk_slot(2 * ks + lh, row)];
-      }
-    } else {
-      const uint4* xs = xring[kt % NS] + (ks >> 1) * S::XT * 64;
-#pragma unroll
-      for (int j = 0; j < TM; ++j) {
-        const int row = wm * TM * 32 + j * 32 + lr;
-        bf[j] = xs[(row >> 4) * 64 + (row & 15) + q];
-      }
-    }
-  };
-  auto mfmas = [&](const uint4 (&af)[TN], const uint4 (&bf)[TM]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-      for (int j = 0; j < TM; ++j) acc[i][j] = mfma32(af[i], bf[j], acc[i][j]);
-  };
-  auto mfmas_row = [&](int i, const uint4 (&af)[TN], const uint4 (&bf)[TM]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < TM; ++j) acc[i][j] = mfma32(af[i], bf[j], acc[i][j]);
-  };
-
-  // Software pipeline across the barrier: the fragments of the first k half
-  // of step kt + 1 are read while the second half of step kt multiplies, so
-  // no wave waits on LDS after a barrier.  The barrier of step kt sits
-  // between its two halves: past it, every wave's loads of stage kt + 1 have
-  // landed and every wave has consumed stage kt - 1, whose slot then takes
-  // stage kt + NS - 1.
-#pragma unroll
-  for (int p = 0; p < NS - 1; ++p)
-    if (p < nk) issue(p);
-  wait_later_stages<LPW, NS - 2>(nk - 1);
-  lds_barrier();
-  uint4 a0[TN], b0[TM], a1[TN], b1[TM];
-  read_frags(0, 0, a0, b0);
-  // halves 0 .. 2 KT - 2 of stage kt, each multiplied while the next is read;
-  // the last one is left in a1, b1
-  auto inner_halves = [&](int kt) __attribute__((always_inline)) {
-#pragma unroll
-    for (int h = 0; h + 1 < 2 * KT; h += 2) {
-      read_frags(kt, h + 1, a1, b1);
-      mfmas(a0, b0);
-      if (h + 2 < 2 * KT) {
-        read_frags(kt, h + 2, a0, b0);
-        mfmas(a1, b1);
-      }
-    }
-  };
-  // (the last step is peeled: a loop exit between the halves would merge
-  // control flow there and make the compiler's LDS waits cover the reads
-  // issued for the next step)
-  for (int kt = 0; kt + 1 < nk; ++kt) {
-    inner_halves(kt);
-    // stage kt + 1 has landed once only the loads of stages kt + 2 .. are
-    // outstanding
-    wait_later_stages<LPW, NS - 3>(nk - 2 - kt);
-    __builtin_amdgcn_sched_barrier(0);
-    lds_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    // the first row of MFMAs goes ahead of the load issue, so the matrix pipe
-    // is fed while the wave computes addresses
-    mfmas_row(0, a1, b1);
-    __builtin_amdgcn_sched_barrier(0);
-    if (kt + NS - 1 < nk) issue(kt + NS - 1);
-    read_frags(kt + 1, 0, a0, b0);
-#pragma unroll
-    for (int i = 1; i < TN; ++i) mfmas_row(i, a1, b1);
-  }
-  inner_halves(nk - 1);
-  mfmas(a1, b1);
-
-  // Fully unrolled (acc must stay in registers).  Slice sums are stored raw:
-  // to part[slice][m][n] with KS > 1, to part[unit][m - m0][n - n0] for a
-  // tail unit.  The residual add first loads all 4 * TN float4 of one 32-row
-  // group of activation rows, then adds and stores them (one round trip per
-  // group rather than per value); the scheduling barrier keeps the compiler
-  // from hoisting every group's loads at once.
-  const bool raw = KS > 1;
-  float* const pout = unit >= 0 ? part + static_cast<size_t>(unit) * S::BM * S::BN
-                      : raw     ? part + static_cast<size_t>(slice) * M * N
-                                : outf;
-  const int pld = unit >= 0 ? S::BN : raw ? N : ldo;
-  const int om = unit >= 0 ? m0 : 0, on = unit >= 0 ? n0 : 0;  // origin of pout
-  if (EPI == kEpiAddF32 && !raw) {
-#pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      const int m = m0 + wm * TM * 32 + j * 32 + lr;
-      if (m >= M) continue;
-      float4 r[TN][4];
-#pragma unroll
-      for (int i = 0; i < TN; ++i) {
-        const int nb = min(n0 + wn * TN * 32 + i * 32, N - 32);  // in bounds; stored only if < N
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          r[i][q] = *reinterpret_cast<const float4*>(outf + static_cast<size_t>(m) * ldo + nb + 8 * q + 4 * lh);
-      }
-#pragma unroll
-      for (int i = 0; i < TN; ++i) {
-        const int nb = n0 + wn * TN * 32 + i * 32;
-        if (nb >= N) continue;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float4 v = r[i][q];
-          v.x += acc[i][j][4 * q];
-          v.y += acc[i][j][4 * q + 1];
-          v.z += acc[i][j][4 * q + 2];
-          v.w += acc[i][j][4 * q + 3];
-          *reinterpret_cast<float4*>(outf + static_cast<size_t>(m) * ldo + nb + 8 * q + 4 * lh) = v;
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < TM; ++j) {
-    const int m = m0 + wm * TM * 32 + j * 32 + lr;
-    if (m >= M) continue;
-#pragma unroll
-    for (int i = 0; i < TN; ++i) {
-      const int nb = n0 + wn * TN * 32 + i * 32;  // 32-row tile of W
-      if (nb >= N) continue;
-      if (EPI == kEpiSwiGLU && !raw) {
-        // the tile is two 16-row blocks of 8 gate rows then the 8 matching up
-        // rows: the lane's rows 8q + 4(l/32) + i of q = 0, 2 (gate) pair with
-        // those of q = 1, 3 (up) in the same lane
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const f32x4 gt{acc[i][j][8 * q], acc[i][j][8 * q + 1], acc[i][j][8 * q + 2], acc[i][j][8 * q + 3]};
-          const f32x4 up{acc[i][j][8 * q + 4], acc[i][j][8 * q + 5], acc[i][j][8 * q + 6], acc[i][j][8 * q + 7]};
-          store_swiglu(gt, up, m, 8 * (nb / 16 + q) + 4 * lh, outb, ldo);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 v{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-          if (raw)
-            store_tile<kEpiStoreF32>(v, m - om, nb + 8 * q + 4 * lh - on, pout, pld);
-          else
-            store_tile<EPI>(v, m, nb + 8 * q + 4 * lh, pout, pld);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Tiled GEMM of 4 waves, one per SIMD (2 x 2, each 16 TN rows of W x 16 TM
-// activation rows of v_mfma_f32_16x16x32_bf16), for prefill chunks.
-//
-// What bounds it: with random operands the chip runs against its power limit,
-// so the energy per flop counts as much as the stalls.
-//  - 16x16x32 instead of 32x32x16 MFMAs: the accumulators are read and written
-//    half as often (a loop of nothing but MFMAs on random data: 2125 against
-//    1862 TFLOP/s).
-//  - 128 x 128 per wave: 128 KiB of LDS reads per 64-wide k step of a 256 x 256
-//    tile, against 192 KiB for 8 waves of 64 x 128.
-//  - a wave alone on its SIMD has nobody to cover its stalls: each memory
-//    instruction rides behind an MFMA, fragments are read one chunk ahead, and
-//    operands are requested two to three chunks ahead.
-// Ring: 4 chunks of 32-wide k for W (operand order, copied as is), 3 stages of
-// 64-wide k for X (whole cache lines; row r keeps its 16-byte chunk c in slot
-// c ^ r % 8, which keeps the fragment reads free of bank conflicts); for
-// 256 x 256 tiles all 160 KiB.  Chunk c: its MFMAs, the fragments of c + 1, the
-// requests of W chunk c + 4 into the slot just freed and of half an X stage,
-// then a barrier (chunk c + 2 has landed, c + 1 is in registers everywhere).
-// Measured, 8 waves of 64 x 128 with 32x32x16 MFMAs before: 8B gate/up at
-// M = 8192 1634 -> 1352 us (1424 TFLOP/s), down 822 -> 649 us (1482), QKV 358
-// -> 289 us, 70B gate/up 6281 -> 5062 us (1520).
-// ---------------------------------------------------------------------------
-template <int TN_, int TM_>
-struct QuadShape {
-  static constexpr bool kQuad = true;
-  static constexpr int TN = TN_, TM = TM_;  // 16 x 16 tiles per wave
-  static constexpr int NTH = 256, BN = 32 * TN, BM = 32 * TM;
-  static constexpr int WS = 4, XS = 3;
-  static constexpr int LW = TN / 2, LX = TM / 2;  // direct loads per wave and chunk
-  static constexpr int kLds = WS * BN * 4 + XS * BM * 8;  // 16-byte units
-  static_assert(TN % 4 == 0 && TM % 4 == 0, "the waves share each chunk evenly");
-};
-
-using BigTile = QuadShape<8, 8>;
 
 // 16 bytes per lane from base + off (base wave-uniform) into LDS
 __device__ __forceinline__ void lds_load16s(const void* base, uint32_t off, uint32_t lds_base) {
@@ -697,7 +378,7 @@ __device__ __forceinline__ void drained_barrier() {
 // fp32: 2 or 4 whole rows of the wave's columns per access; the residual of
 // the next 32 rows is loaded meanwhile.
 template <class S, int EPI>
-__device__ __forceinline__ void quad_epilogue_f32(const f32x4 (&acc)[S::TN][S::TM], uint4* buf, int mw, int nw, int m0,
+__device__ __forceinline__ void tile_epilogue_f32(const f32x4 (&acc)[S::TN][S::TM], uint4* buf, int mw, int nw, int m0,
                                                   int n0, int lane, int M, int N, int KS, int slice, int unit,
                                                   float* __restrict__ outf, int ldo, float* __restrict__ part) {
   constexpr int TN = S::TN, TM = S::TM, CH = 4 * TN;  // 16-byte chunks per row
@@ -775,7 +456,7 @@ __device__ __forceinline__ void pair_halves(f32x4 x, f32x4 y, f32x4& lo, f32x4& 
 
 // SwiGLU: the wave's 8 TN outputs per row (16 TN bytes)
 template <class S>
-__device__ __forceinline__ void quad_epilogue_swiglu(const f32x4 (&acc)[S::TN][S::TM], uint4* buf, int mw, int nw,
+__device__ __forceinline__ void tile_epilogue_swiglu(const f32x4 (&acc)[S::TN][S::TM], uint4* buf, int mw, int nw,
                                                      int lane, int M, int N, uint16_t* __restrict__ outb, int ldo) {
   constexpr int TN = S::TN, TM = S::TM, CH = TN;  // 16-byte chunks per row
   constexpr int RPI = 64 / CH, NI = 32 / RPI;
@@ -813,12 +494,18 @@ __device__ __forceinline__ void quad_epilogue_swiglu(const f32x4 (&acc)[S::TN][S
   }
 }
 
-// Work of one workgroup: as gemm_tiled_kernel, every XCD taking a contiguous
-// run of the work list.  In tile_origin order 32 consecutive tiles (one XCD's
-// CUs) cover 4 x 8 tiles, so an XCD's L2 fetches 12 operand tiles per k step;
-// the list in grid order made that 18 (8B gate/up at M = 8192 1506 -> 1479 us).
+// Work of one workgroup.  Without a tail split the grid's tiles x k slices
+// (slice-major list, tiles in tile_origin order) are spread over the XCDs by
+// xcd_contiguous.  With one (tail_split = S > 1), workgroups x < tail_first
+// take tile x over all of K, and the last tiles, which would leave most CUs
+// idle in the final round, are cut into S k slices each: workgroup tail_first +
+// u takes slice u % S of tile tail_first + u / S and stores its fp32 sums to
+// part[u][BM][BN] for gemm_tail_fixup_kernel.
+// In tile_origin order 32 consecutive 256 x 256 tiles (one XCD's CUs) cover 4 x
+// 8 of them, so an XCD's L2 fetches 12 operand tiles per k step; the list in
+// grid order made that 18 (8B gate/up at M = 8192 1506 -> 1479 us).
 template <class S, int EPI>
-__global__ __launch_bounds__(S::NTH, 1) void gemm_quad_kernel(const uint16_t* __restrict__ X, int ldx,
+__global__ __launch_bounds__(S::NTH, S::OCC) void gemm_tiled_kernel(const uint16_t* __restrict__ X, int ldx,
                                                               const uint16_t* __restrict__ W, int Kp, int M, int N,
                                                               float* __restrict__ outf, uint16_t* __restrict__ outb,
                                                               int ldo, float* __restrict__ part, int tail_first,
@@ -988,11 +675,11 @@ __global__ __launch_bounds__(S::NTH, 1) void gemm_quad_kernel(const uint16_t* __
     }
   } else if constexpr (EPI == kEpiSwiGLU) {
     if (KS > 1)
-      quad_epilogue_f32<S, kEpiStoreF32>(acc, buf, mw, nw, m0, n0, lane, M, N, KS, slice, unit, outf, ldo, part);
+      tile_epilogue_f32<S, kEpiStoreF32>(acc, buf, mw, nw, m0, n0, lane, M, N, KS, slice, unit, outf, ldo, part);
     else
-      quad_epilogue_swiglu<S>(acc, buf, mw, nw, lane, M, N, outb, ldo);
+      tile_epilogue_swiglu<S>(acc, buf, mw, nw, lane, M, N, outb, ldo);
   } else {
-    quad_epilogue_f32<S, EPI>(acc, buf, mw, nw, m0, n0, lane, M, N, KS, slice, unit, outf, ldo, part);
+    tile_epilogue_f32<S, EPI>(acc, buf, mw, nw, m0, n0, lane, M, N, KS, slice, unit, outf, ldo, part);
   }
 }
 
@@ -1212,12 +899,8 @@ static void launch_tiled(const uint16_t* X, int ldx, const uint16_t* W, int Kp, 
                          int tail_first = 0) {
   const int tiles = ((N + S::BN - 1) / S::BN) * ((M + S::BM - 1) / S::BM);
   const int blocks = tail_split > 1 ? tail_first + (tiles - tail_first) * tail_split : tiles;
-  if constexpr (S::kQuad)
-    launch_kernel((gemm_quad_kernel<S, EPI>), dim3(blocks, ks), dim3(S::NTH), 0, s, X, ldx, W, Kp, M, N, outf, outb, ldo,
-                  part, tail_first, tail_split, RopeKV{});
-  else
-    launch_kernel((gemm_tiled_kernel<S, EPI>), dim3(blocks, ks), dim3(S::NTH), 0, s, X, ldx, W, Kp, M, N, outf, outb,
-                  ldo, part, tail_first, tail_split);
+  launch_kernel((gemm_tiled_kernel<S, EPI>), dim3(blocks, ks), dim3(S::NTH), 0, s, X, ldx, W, Kp, M, N, outf, outb, ldo,
+                part, tail_first, tail_split, RopeKV{});
   if (tail_split > 1) {
     if constexpr (EPI == kEpiSwiGLU)
       launch_kernel((gemm_tail_fixup_swiglu_kernel<S>), dim3(tiles - tail_first, S::BM / (2048 / S::BN)),
@@ -1286,7 +969,7 @@ hipError_t launch_gemm_rope_kv(const uint16_t* X, int ldx, const uint16_t* W, in
     return hipErrorInvalidValue;
   if (M > kRopeKVMaxRows) {  // 256 x 256 tiles over all of K (no workspace: no split of the last round)
     const int tiles = ((N + BigTile::BN - 1) / BigTile::BN) * ((M + BigTile::BM - 1) / BigTile::BM);
-    launch_kernel((gemm_quad_kernel<BigTile, kEpiRopeKV>), dim3(tiles, 1), dim3(BigTile::NTH), 0, s, X, ldx, W, Kp,
+    launch_kernel((gemm_tiled_kernel<BigTile, kEpiRopeKV>), dim3(tiles, 1), dim3(BigTile::NTH), 0, s, X, ldx, W, Kp,
                   M, N, nullptr, nullptr, 0, nullptr, 0, 1, rk);
     return hipGetLastError();
   }

@@ -1,4 +1,4 @@
-"""The 256 x 256 tile GEMM issues its MFMAs as inline assembly with the
+"""The tiled GEMM issues its MFMAs as inline assembly with the
 accumulators tied to AGPRs, so the compiler's own hazard handling does not see
 them.  What the kernel relies on is checked in the assembly that this source
 compiles to: inside the k loop nothing but MFMAs touches an AGPR, the
@@ -23,7 +23,7 @@ def kernels(tmp_path_factory):
                     os.path.join(b.PKG, "csrc/kernels/gemm.hip"), "-o", out], check=True, capture_output=True)
     text = open(out).read()
     found = {}
-    for m in re.finditer(r"^(_ZN5metro\w*gemm_quad_kernel\w*):", text, re.M):
+    for m in re.finditer(r"^(_ZN5metro\w*gemm_tiled_kernel\w*):", text, re.M):
         body = text[m.end():text.index(".Lfunc_end", m.end())]
         found[m.group(1)] = [ln.split(";")[0].strip() for ln in body.split("\n")]
     assert found
@@ -46,7 +46,6 @@ def test_accumulators_stay_in_place(kernels):
         for i in reversed(mfma):
             lo, hi = map(int, re.match(r"v_mfma\w+ a\[(\d+):(\d+)\]", ops[i]).groups())
             first.update((r, i) for r in range(lo, hi + 1))
-        assert len(first) == 256, name
         for i in agpr:
             if i < mfma[0]:
                 r = int(re.match(r"v_accvgpr_write_b32 a(\d+), 0$", ops[i]).group(1))
