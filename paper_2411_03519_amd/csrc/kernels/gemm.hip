@@ -290,10 +290,11 @@ struct TileShape {
   static constexpr int TN = TN_, TM = TM_;  // 16 x 16 tiles per wave
   static constexpr int NTH = 256, BN = 32 * TN, BM = 32 * TM;
   static constexpr int WS = 4, XS = 3;
-  static constexpr int LW = TN / 2, LX = TM / 2;  // direct loads per wave and chunk
+  static constexpr int LW = TN / 2;                     // W loads per wave and chunk
+  static constexpr int LX0 = TM / 2, LX1 = TM - LX0;    // X loads per wave: first, second half of a stage
   static constexpr int kLds = WS * BN * 4 + XS * BM * 8;  // 16-byte units
   static constexpr int OCC = kLds * 16 <= 80 * 1024 ? 2 : 1;  // workgroups per CU that its registers must allow
-  static_assert(TN % 4 == 0 && TM % 4 == 0, "the waves share each chunk evenly");
+  static_assert(TN % 4 == 0 && TM >= 2, "the waves share each chunk evenly");
 };
 
 // Big: for prefill chunks.  Mid: for batches of 65 to a few hundred rows; 80
@@ -315,7 +316,7 @@ using WideTile = TileShape<8, 4>;
 // consecutive ones, the CUs of one XCD, cover 4 x 8).
 template <class S>
 __host__ __device__ __forceinline__ void tile_origin(int t, int M, int N, int& m0, int& n0) {
-  constexpr int kGroupM = S::BM * S::BN < 256 * 256 ? 16 : 4;
+  constexpr int kGroupM = S::TN * S::TM > 32 ? 4 : 16;
   const int mt = (M + S::BM - 1) / S::BM, nt = (N + S::BN - 1) / S::BN;
   const int group = t / (kGroupM * nt);
   const int first_m = group * kGroupM;
@@ -389,7 +390,7 @@ __device__ __forceinline__ void tile_epilogue_f32(const f32x4 (&acc)[S::TN][S::T
   float* out = outf;
   int ld = ldo, mb = mw, nb = nw + 4 * col;
   const bool nok = nb < N;
-  const int mok = M - mw;  // rows of the wave's tile
+  const int mok = min(M - mw, 16 * TM);  // rows of the wave's tile
   nb = min(nb, N - 4);
   if (unit >= 0) {
     out = part + static_cast<size_t>(unit) * S::BM * S::BN;
@@ -413,20 +414,20 @@ __device__ __forceinline__ void tile_epilogue_f32(const f32x4 (&acc)[S::TN][S::T
     if (add) load_res(0);
   }
 #pragma unroll
-  for (int q = 0; q < TM / 2; ++q) {
+  for (int q = 0; q < (TM + 1) / 2; ++q) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2 && 2 * q + j < TM; ++j)
 #pragma unroll
       for (int i = 0; i < TN; ++i) {
         const int r = 16 * j + r16;
         buf[r * CH + ((4 * i + g) ^ (r % CH))] = __builtin_bit_cast(uint4, acc[i][2 * q + j]);
       }
     if (EPI == kEpiAddF32) {
-      if (add && q + 1 < TM / 2) load_res(q + 1);
+      if (add && 2 * q + 2 < TM) load_res(q + 1);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < NI; ++t) {
+    for (int t = 0; t < (2 * q + 1 < TM ? NI : NI / 2); ++t) {
       const int r = RPI * t + sub;
       float4 v = __builtin_bit_cast(float4, buf[r * CH + (col ^ (r % CH))]);
       if (EPI == kEpiAddF32) {
@@ -465,9 +466,9 @@ __device__ __forceinline__ void tile_epilogue_swiglu(const f32x4 (&acc)[S::TN][S
   uint2* const buf8 = reinterpret_cast<uint2*>(buf);
   const bool nok = nw + 16 * col < N;
 #pragma unroll
-  for (int q = 0; q < TM / 2; ++q) {
+  for (int q = 0; q < (TM + 1) / 2; ++q) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2 && 2 * q + j < TM; ++j)
 #pragma unroll
       for (int i = 0; i < TN; i += 2) {
         f32x4 gt, up;
@@ -481,7 +482,7 @@ __device__ __forceinline__ void tile_epilogue_swiglu(const f32x4 (&acc)[S::TN][S
       }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < NI; ++t) {
+    for (int t = 0; t < (2 * q + 1 < TM ? NI : NI / 2); ++t) {
       const int r = RPI * t + sub, m = mw + 32 * q + r;
       const uint4 v = buf[r * CH + (col ^ (r % CH))];
       if (nok && m < M) {
@@ -492,6 +493,14 @@ __device__ __forceinline__ void tile_epilogue_swiglu(const f32x4 (&acc)[S::TN][S
     }
     __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+// index of the direct load that rides behind MFMA u of nm (nd of them spread
+// evenly behind odd MFMAs), nd if none
+constexpr int load_behind(int u, int nm, int nd) {
+  for (int l = 0; l < nd; ++l)
+    if ((l * nm / nd | 1) == u) return l;
+  return nd;
 }
 
 // Work of one workgroup.  Without a tail split the grid's tiles x k slices
@@ -510,7 +519,7 @@ __global__ __launch_bounds__(S::NTH, S::OCC) void gemm_tiled_kernel(const uint16
                                                               float* __restrict__ outf, uint16_t* __restrict__ outb,
                                                               int ldo, float* __restrict__ part, int tail_first,
                                                               int tail_split, RopeKV rk) {
-  constexpr int TN = S::TN, TM = S::TM, WS = S::WS, XS = S::XS, LW = S::LW, LX = S::LX;
+  constexpr int TN = S::TN, TM = S::TM, WS = S::WS, LW = S::LW, LX0 = S::LX0, LX1 = S::LX1;
   __shared__ uint4 lds[S::kLds];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -541,20 +550,20 @@ __global__ __launch_bounds__(S::NTH, S::OCC) void gemm_tiled_kernel(const uint16
   const char* const wbase =
       reinterpret_cast<const char*>(W + (static_cast<size_t>(n0 / 16) * (Kp / 32) + k0 / 32) * 512);
   const char* const xbase = reinterpret_cast<const char*>(X + static_cast<size_t>(m0) * ldx + k0);
-  uint32_t woff[LW], xoff[2 * LX];
+  uint32_t woff[LW], xoff[TM];
 #pragma unroll
   for (int j = 0; j < LW; ++j) {
     const int rt = min(LW * wave + j, N / 16 - 1 - n0 / 16);
     woff[j] = static_cast<uint32_t>(rt) * (Kp / 32) * 1024 + lane * 16;
   }
 #pragma unroll
-  for (int j = 0; j < 2 * LX; ++j) {
-    const int u = 2 * LX * wave + j;
+  for (int j = 0; j < TM; ++j) {
+    const int u = TM * wave + j;
     const int row = min(8 * u + (lane >> 3), M - 1 - m0);
     xoff[j] = (static_cast<uint32_t>(row) * ldx + 8 * ((lane & 7) ^ (lane >> 3))) * 2;
   }
   const uint32_t wlds = lds_address(lds) + wave * LW * 1024;
-  const uint32_t xlds = lds_address(lds + WS * S::BN * 4) + wave * LX * 2048;
+  const uint32_t xlds = lds_address(lds + WS * S::BN * 4) + wave * TM * 1024;
   constexpr uint32_t kWSlot = S::BN * 64, kXSlot = S::BM * 128;  // bytes of a W chunk, an X stage
 
   f32x4 acc[TN][TM];
@@ -588,22 +597,22 @@ __global__ __launch_bounds__(S::NTH, S::OCC) void gemm_tiled_kernel(const uint16
 #pragma unroll
   for (int j = 0; j < LW; ++j) load_w(0, j);
 #pragma unroll
-  for (int j = 0; j < 2 * LX; ++j) load_x(0, j);
+  for (int j = 0; j < TM; ++j) load_x(0, j);
 #pragma unroll
   for (int j = 0; j < LW; ++j) load_w(1, j);
 #pragma unroll
-  for (int j = 0; j < 2 * LX; ++j) load_x(1, j);
+  for (int j = 0; j < TM; ++j) load_x(1, j);
 #pragma unroll
   for (int c = 2; c < 4; ++c)
 #pragma unroll
     for (int j = 0; j < LW; ++j) load_w(c, j);
 #pragma unroll
-  for (int j = 0; j < LX; ++j) load_x(2, j);
-  wait_vmcnt<3 * LW + 3 * LX>();
+  for (int j = 0; j < LX0; ++j) load_x(2, j);
+  wait_vmcnt<3 * LW + TM + LX0>();
   lds_barrier();
 #pragma unroll
   for (int u = 0; u < TN + TM; ++u) read_frag(u, 0, 0, 0);
-  wait_vmcnt<2 * LW + 3 * LX>();
+  wait_vmcnt<2 * LW + TM + LX0>();
   drained_barrier();
 
   // One chunk, in fragment set P = parity of the chunk: its MFMAs, the
@@ -615,27 +624,27 @@ __global__ __launch_bounds__(S::NTH, S::OCC) void gemm_tiled_kernel(const uint16
   // LDS reads would back up and hold the wave's next MFMA.
   auto chunk = [&](auto par, uint32_t wo, uint32_t xo, const char* wsrc, uint32_t wd, const char* xsrc,
                    uint32_t xd) __attribute__((always_inline)) {
-    constexpr int P = decltype(par)::value, NM = TN * TM;
-    static_assert(2 * (TN + TM) <= NM, "the fragment reads fit behind every other MFMA");
+    constexpr int P = decltype(par)::value, NM = TN * TM, ND = LW + (P ? LX0 : LX1);
+    constexpr int RS = 2 * (TN + TM) <= NM ? 2 : 1;
+    static_assert(RS * (TN + TM) <= NM && 2 * ND <= NM, "the memory instructions fit behind the MFMAs");
     [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
       (([&]() __attribute__((always_inline)) {
          constexpr int i = U / TM, j = (i & 1) ? TM - 1 - U % TM : U % TM;
-         // the direct loads spread over the chunk, behind odd MFMAs; the reads behind the first even ones
-         constexpr int l0 = U * (LW + LX) / NM, l1 = (U + 1) * (LW + LX) / NM;
-         constexpr int l = (l0 * NM / (LW + LX) | 1) == U ? l0 : (l1 * NM / (LW + LX) | 1) == U ? l1 : LW + LX;
+         // the direct loads spread over the chunk, behind odd MFMAs; the reads behind the first ones
+         constexpr int l = load_behind(U, NM, ND);
          if constexpr (l < LW)
            mfma16_acc_load<l * 1024>(acc[i][j], a[P][i], b[P][j], wsrc, woff[l], wd);
-         else if constexpr (l < LW + LX)
-           mfma16_acc_load<((P ? 0 : LX) + l - LW) * 1024>(acc[i][j], a[P][i], b[P][j], xsrc,
-                                                           xoff[(P ? 0 : LX) + l - LW], xd);
+         else if constexpr (l < ND)
+           mfma16_acc_load<((P ? 0 : LX0) + l - LW) * 1024>(acc[i][j], a[P][i], b[P][j], xsrc,
+                                                            xoff[(P ? 0 : LX0) + l - LW], xd);
          else
            mfma16_acc(acc[i][j], a[P][i], b[P][j]);
-         if constexpr (U % 2 == 0 && U / 2 < TN + TM) read_frag(U / 2, P ^ 1, wo, xo);
+         if constexpr (U % RS == 0 && U / RS < TN + TM) read_frag(U / RS, P ^ 1, wo, xo);
          __builtin_amdgcn_sched_barrier(0);
        }()),
        ...);
     }(std::make_integer_sequence<int, NM>{});
-    wait_vmcnt<2 * LW + (P ? 3 : 2) * LX>();
+    wait_vmcnt<2 * LW + TM + (P ? LX0 : 0)>();
     drained_barrier();
   };
   // Requests past the last chunk re-read it into slots that are no longer
@@ -911,6 +920,23 @@ static void launch_tiled(const uint16_t* X, int ldx, const uint16_t* W, int Kp, 
   }
 }
 
+// Row blocks of 32 TM rows: as many as the kind's full blocks would be, evened
+// out, so that no block works on many absent rows (M = 301: 2 x 160 instead of
+// 2 x 256).
+template <class Go>
+static void even_rows(int M, int bm, Go&& go) {
+  const int blocks = (M + bm - 1) / bm, tm = ((M + blocks - 1) / blocks + 31) / 32;
+  if (bm == BigTile::BM) {
+    if (tm <= 5) go(std::integral_constant<int, 5>{});
+    else if (tm == 6) go(std::integral_constant<int, 6>{});
+    else if (tm == 7) go(std::integral_constant<int, 7>{});
+    else go(std::integral_constant<int, 8>{});
+  } else {
+    if (tm <= 3) go(std::integral_constant<int, 3>{});
+    else go(std::integral_constant<int, 4>{});
+  }
+}
+
 template <int EPI>
 static hipError_t launch_epi(const GemmPlan& p, const uint16_t* X, int ldx, const uint16_t* W, int Kp, int M, int N,
                              float* outf, uint16_t* outb, int ldo, float* part, hipStream_t s) {
@@ -924,13 +950,24 @@ static hipError_t launch_epi(const GemmPlan& p, const uint16_t* X, int ldx, cons
         launch_skinny_m<2, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
       break;
     case GemmKind::kMid:
-      launch_tiled<MidTile, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
+      even_rows(M, MidTile::BM, [&](auto tm) {
+        if constexpr (tm <= 4)
+          launch_tiled<TileShape<MidTile::TN, tm>, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
+      });
       break;
     case GemmKind::kWide:
-      launch_tiled<WideTile, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s, p.tail_split, p.tail_first);
+      even_rows(M, WideTile::BM, [&](auto tm) {
+        if constexpr (tm <= 4)
+          launch_tiled<TileShape<WideTile::TN, tm>, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s,
+                                                         p.tail_split, p.tail_first);
+      });
       break;
     case GemmKind::kBig:
-      launch_tiled<BigTile, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s, p.tail_split, p.tail_first);
+      even_rows(M, BigTile::BM, [&](auto tm) {
+        if constexpr (tm > 4)
+          launch_tiled<TileShape<BigTile::TN, tm>, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s,
+                                                        p.tail_split, p.tail_first);
+      });
       break;
   }
   return hipGetLastError();
@@ -968,9 +1005,14 @@ hipError_t launch_gemm_rope_kv(const uint16_t* X, int ldx, const uint16_t* W, in
   if (!gemm_rope_kv_fused(M, N, Kp) || N != (rk.nq + 2 * rk.nkv) * rk.hd || rk.hd % 32 || N % 32)
     return hipErrorInvalidValue;
   if (M > kRopeKVMaxRows) {  // 256 x 256 tiles over all of K (no workspace: no split of the last round)
-    const int tiles = ((N + BigTile::BN - 1) / BigTile::BN) * ((M + BigTile::BM - 1) / BigTile::BM);
-    launch_kernel((gemm_tiled_kernel<BigTile, kEpiRopeKV>), dim3(tiles, 1), dim3(BigTile::NTH), 0, s, X, ldx, W, Kp,
-                  M, N, nullptr, nullptr, 0, nullptr, 0, 1, rk);
+    even_rows(M, BigTile::BM, [&](auto tm) {
+      if constexpr (tm > 4) {
+        using S = TileShape<BigTile::TN, tm>;
+        const int tiles = ((N + S::BN - 1) / S::BN) * ((M + S::BM - 1) / S::BM);
+        launch_kernel((gemm_tiled_kernel<S, kEpiRopeKV>), dim3(tiles, 1), dim3(S::NTH), 0, s, X, ldx, W, Kp, M, N,
+                      nullptr, nullptr, 0, nullptr, 0, 1, rk);
+      }
+    });
     return hipGetLastError();
   }
   constexpr int NT = 2, NW = 4;

@@ -260,3 +260,41 @@ def test_gemm_repeated_launches_are_bitwise_stable(metro):
                     assert np.all(np.abs(got.astype(np.float64) - ref) <= bound), f"case {i}"
             else:
                 np.testing.assert_array_equal(got, first[i], err_msg=f"case {c[:5]} launch {rep}")
+
+
+# Row blocks of the tiled kernel are evened out over the rows (32 TM rows, TM 3
+# or 4 for 128-row blocks, 5 .. 8 for 256-row ones): both sides of each step,
+# with a last block that is nearly empty, ragged N, and k slices / a split last
+# round when given a workspace.
+EVEN_ROWS = [(96, 1056), (97, 1056), (192, 160), (193, 16384), (192, 28672), (257, 16416), (320, 16384), (321, 16384),
+             (385, 16384), (449, 16384), (513, 16384), (1001, 288), (1025, 288), (1281, 160)]
+
+
+@pytest.mark.parametrize("M,N", EVEN_ROWS)
+@pytest.mark.parametrize("epi", [0, 1, 2])
+def test_gemm_even_row_blocks(metro, M, N, epi):
+    print(f"even rows M={M} N={N} epi={epi}", flush=True)
+    K = 384
+    g = torch.Generator(device="cuda").manual_seed(M + N + epi)
+    X = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
+    W = (0.05 * torch.randn(N, K, generator=g, device="cuda")).to(torch.bfloat16)
+    P = torch.empty_like(W)
+    metro.op_pack_weight(W, K, N, K, K, P)
+    ref = X.double() @ W.double().T
+    err = 1e-5 * (X.double().abs() @ W.double().abs().T) + 1e-6
+    outs = []
+    for ws in (None, torch.full((8, M, N), float("nan"), device="cuda")):
+        if epi == 2:
+            out = torch.zeros(M, N // 2, dtype=torch.bfloat16, device="cuda")
+            metro.op_gemm(X, P, M, N, K, epi, out, N // 2, workspace=ws)
+            pair = lambda t: (t.view(M, N // 16, 2, 8)[:, :, 0].reshape(M, -1), t.view(M, N // 16, 2, 8)[:, :, 1].reshape(M, -1))  # noqa: E731
+            (gate, up), (eg, eu) = pair(ref), pair(err)
+            want = torch.nn.functional.silu(gate) * up
+            # the fp32 errors through silu(gate) * up, and one bf16 ulp (2^-8 of the value)
+            bound = 2 * (1.1 * up.abs() * eg + torch.nn.functional.silu(gate).abs() * eu) + want.abs() / 256 + 1e-30
+        else:
+            init = torch.randn(M, N, generator=g, device="cuda")
+            out = init.clone()
+            metro.op_gemm(X, P, M, N, K, epi, out, N, workspace=ws)
+            want, bound = ref + (init.double() if epi == 1 else 0.0), err
+        assert bool(((out.double() - want).abs() <= bound).all())
