@@ -31,7 +31,7 @@
 // Prefill (flash attention): one workgroup = (query block, kv head); the K and
 // V pages of the block's visible context go through LDS in pairs, by direct
 // loads into a 4-stage ring (three pairs in flight while one is consumed), and
-// are shared by the eight waves (two per SIMD); causal masking per element.
+// are shared by the eight waves; causal masking per element.
 #include "common.h"
 #include "kernels.h"
 
@@ -49,6 +49,19 @@ __device__ __forceinline__ f32x4 mfma_k32(uint4 a, uint4 b, f32x4 c) {
 __device__ __forceinline__ f32x4 mfma_k16(uint2 a, uint2 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c,
                                                    0, 0, 0);
+}
+
+// The upper half of a trades places with the lower half of b.  An MFMA that
+// reads the result has to be at least two instructions away (wait states that
+// the compiler does not add behind inline assembly): NOPS of them are part of
+// the block, the caller keeps the others between.
+template <int NOPS>
+__device__ __forceinline__ void swap_halves(uint4& a, uint4& b) {
+  if constexpr (NOPS == 2)
+    asm volatile("v_swap_b32 %0, %2\n\tv_swap_b32 %1, %3\n\ts_nop 1"
+                 : "+v"(a.z), "+v"(a.w), "+v"(b.x), "+v"(b.y));
+  else
+    asm volatile("v_swap_b32 %0, %2\n\tv_swap_b32 %1, %3" : "+v"(a.z), "+v"(a.w), "+v"(b.x), "+v"(b.y));
 }
 
 // 2^x by the hardware instruction (v_exp_f32, about 1 ulp).  exp2f adds a
@@ -299,25 +312,28 @@ __device__ __attribute__((noinline)) void zero_v_past(uint32_t* vt, int n0, int 
 // Prefill (flash attention over pages)
 // ===========================================================================
 
-// Query columns of one 16-wide MFMA tile: 16/G tokens x G heads.
-// Waves x query tiles per wave (16 tiles = 256 query columns per block): at
-// head dim 128, 16 waves (four per SIMD) of one tile each, since 8 waves of
-// two tiles (208 VGPRs) left only two waves per SIMD to hide the latency of
-// each tile's chain of score MFMAs, softmax and output MFMAs; at head dim 64
-// a page tile is too small to split over 16 waves, so 8 waves of two tiles.
-template <int HD>
-struct PrefillShape {
-  static constexpr int NW = HD >= 128 ? 16 : 8, NQ = 16 / NW;
-};
-constexpr int kPrefillTilesPerBlock = 16;
-constexpr int kPrefillPageIds = 512;  // page ids staged in LDS (contexts up to 8192 keys)
+// Query columns of one 16-wide MFMA tile: 16/G tokens x G heads.  A block is
+// 8 waves of one tile (128 query columns).  Per page pair and wave the matrix
+// core needs 384 cycles and the vector ALU about as many (scale, exp2, hi/lo
+// split, sum), so waves in different phases have to overlap: two such blocks,
+// each with its own barriers, fit a CU (64 KiB ring, up to 128 VGPRs), where
+// one block of 16 waves (head dim 128) or 8 of two tiles (64) filled it before.
+// 4 waves per block read the pages from L2 too often (two blocks per CU all the
+// same); two tiles per wave with 4 waves halve the LDS reads and gain nothing.
+// Blocks run last rows first: those see the most keys, and the short ones fill
+// the end of the launch.
+// Measured (nq 32, nkv 8, hd 128; us, before -> now): chunks of 3500 and 3800
+// after 2000 and 8000 keys 1450 -> 1237; 25 prompts of 256 .. 2416 862 -> 699;
+// one of 2048 94 -> 67; 161 rows after 448 keys 29.6 -> 20.2; hd 64, 3 x 700
+// after 1000 81 -> 60.
+constexpr int kPrefillWaves = 8;
 
-template <int HD, int G, int NW, int NQ>
-__global__ __launch_bounds__(NW * 64) void attn_prefill_kernel(PrefillAttnArgs a) {
+template <int HD, int G>
+__global__ __launch_bounds__(kPrefillWaves * 64, 4) void attn_prefill_kernel(PrefillAttnArgs a) {
+  constexpr int NW = kPrefillWaves;
   constexpr int KQ = HD / 32;
   constexpr int NT = HD / 16;
-  constexpr int TPT = 16 / G;         // tokens per tile
-  constexpr int TPW = NQ * TPT;       // tokens per wave
+  constexpr int TPW = 16 / G;         // tokens per tile
   constexpr int PCH = kPage * HD / 8;  // 16-byte chunks of one K (or V^T) page tile
   constexpr int WPT = NW / 4;         // waves bringing each of the 4 tiles of a stage
   constexpr int LPW = PCH / WPT / 64;  // direct loads per wave per stage
@@ -329,7 +345,7 @@ __global__ __launch_bounds__(NW * 64) void attn_prefill_kernel(PrefillAttnArgs a
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int col = lane & 15, grp = lane >> 4;
-  const int bi = blockIdx.x / a.nkv, h = blockIdx.x % a.nkv;
+  const int bi = a.n_blocks - 1 - blockIdx.x / a.nkv, h = blockIdx.x % a.nkv;
   const int item = a.blocks[3 * bi], row0 = a.blocks[3 * bi + 1], nrows = a.blocks[3 * bi + 2];
   const int32_t* bt = a.bt + a.item_bt[item];
   const int last_pos = a.pos[row0 + nrows - 1];
@@ -338,31 +354,20 @@ __global__ __launch_bounds__(NW * 64) void attn_prefill_kernel(PrefillAttnArgs a
   const int n_pairs = (n_pages + 1) / 2;
   const float qscale = a.scale * kLog2e;
 
-  // this lane's query column in each tile
-  int qpos[NQ], qrow[NQ];
-  bool qok[NQ];
-  uint4 qf[NQ][KQ];
+  // this lane's query column
+  const int tok = wave * TPW + col / G;
+  const bool qok = tok < nrows;
+  const int qrow = row0 + (qok ? tok : 0);
+  const int qpos = qok ? a.pos[qrow] : -1;
+  uint4 qf[KQ];
+  const uint16_t* qp = a.q + (static_cast<size_t>(qrow) * a.nq + h * G + col % G) * HD + 8 * grp;
 #pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    const int tok = wave * TPW + n * TPT + col / G;
-    qok[n] = tok < nrows;
-    qrow[n] = row0 + (qok[n] ? tok : 0);
-    qpos[n] = qok[n] ? a.pos[qrow[n]] : -1;
-    const uint16_t* qp = a.q + (static_cast<size_t>(qrow[n]) * a.nq + h * G + col % G) * HD + 8 * grp;
-#pragma unroll
-    for (int i = 0; i < KQ; ++i)
-      qf[n][i] = qok[n] ? *reinterpret_cast<const uint4*>(qp + 32 * i) : make_uint4(0, 0, 0, 0);
-  }
+  for (int i = 0; i < KQ; ++i) qf[i] = qok ? *reinterpret_cast<const uint4*>(qp + 32 * i) : make_uint4(0, 0, 0, 0);
 
-  f32x4 o[NQ][NT];
-  float m[NQ], l[NQ];
+  f32x4 o[NT];
+  float m = kNegBig, l = 0.f;
 #pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    m[n] = kNegBig;
-    l[n] = 0.f;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) o[n][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int t = 0; t < NT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // Waves WPT*t .. WPT*t + WPT-1 bring the parts of tile t of every stage:
   // the K (t < 2) or V^T (t >= 2) tile of page 2*pair + (t & 1).  The absent
@@ -371,19 +376,20 @@ __global__ __launch_bounds__(NW * 64) void attn_prefill_kernel(PrefillAttnArgs a
   const int tile = wave / WPT, piece = wave % WPT;
   const size_t part = kv_offset(0, tile >> 1, a.nkv, h, 0, HD, 0) + piece * (PCH / WPT) * 8;
   const size_t pstride = static_cast<size_t>(2) * a.nkv * kPage * HD;
-  // The block's page ids go to LDS once, so that a stage's load issue waits
-  // on an LDS read rather than on a block-table load from memory (pages past
-  // the table's capacity are still read from the block table).
-  __shared__ int32_t page_ids[kPrefillPageIds];
-  for (int i = tid; i < min(n_pages, kPrefillPageIds); i += NW * 64) page_ids[i] = bt[i];
-  __syncthreads();
+  // Lane l holds the id of this wave's page of pair 64 k + l, so that a stage's
+  // load issue waits on no memory lookup; the wait for the ids is kept inside
+  // the branch (past it, it would also wait for the loads just issued).
+  int pid = 0;
   auto issue = [&](int pair) __attribute__((always_inline)) {
-    const int pi = min(2 * pair + (tile & 1), n_pages - 1);
-    const int id = pi < kPrefillPageIds ? page_ids[pi] : bt[pi];
-    const uint16_t* src = a.kv + static_cast<size_t>(id) * pstride + part + 8 * lane;
+    if ((pair & 63) == 0) {
+      pid = bt[min(2 * (pair + lane) + (tile & 1), n_pages - 1)];
+      asm volatile("" : "+v"(pid));
+    }
+    const int id = __builtin_amdgcn_readlane(pid, pair & 63);
+    const uint16_t* src = a.kv + static_cast<size_t>(id) * pstride + part;
     const uint32_t dst = lds_address(&ring[pair % NS][tile][piece * (PCH / WPT)]);
 #pragma unroll
-    for (int c = 0; c < LPW; ++c) lds_load16(src + 512 * c, dst + 1024 * c);
+    for (int c = 0; c < LPW; ++c) lds_load16s(src + 512 * c, 16 * lane, dst + 1024 * c);
   };
 
   issue(0);
@@ -408,115 +414,103 @@ __global__ __launch_bounds__(NW * 64) void attn_prefill_kernel(PrefillAttnArgs a
       __syncthreads();
     }
 
-    // K operand of both pages (A of S^T): key row col, dims 32i + 8grp .. +7;
-    // V^T operand over the pair: dims of tile t, keys 4grp .. 4grp+3 of each
-    // page (held for all query tiles when the wave has several, else read
-    // from LDS as each output tile needs it)
-    uint4 kf[2][KQ];
+    // scores q.k, K operand (A of S^T): key row col, dims 32i + 8grp .. +7
+    float sv[2][4];
+#pragma unroll
+    for (int pg = 0; pg < 2; ++pg) {
+      f32x4 sc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < KQ; ++i) sc = mfma_k32(st[pg][64 * i + lane], qf[i], sc);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sv[pg][r] = sc[r];
+    }
+    // (keys of this pair visible to every query of the block need no mask)
+    if ((2 * pair + 2) * kPage - 1 > first_pos) {
+#pragma unroll
+      for (int pg = 0; pg < 2; ++pg)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if ((2 * pair + pg) * kPage + 4 * grp + r > qpos) sv[pg][r] = -INFINITY;
+    }
+    // The reference max m only moves when some column's max exceeds it by
+    // more than 8 (a factor 2^8): o and l carry the same scale, so their
+    // quotient is unchanged, and p = 2^(s - m) stays below 2^8.  Whether any
+    // score does is read off the exponents s*scale - m themselves, so the
+    // column maxima (a cross-lane reduction) are formed only when m moves.
+    float e[2][4];
 #pragma unroll
     for (int pg = 0; pg < 2; ++pg)
 #pragma unroll
-      for (int i = 0; i < KQ; ++i) kf[pg][i] = st[pg][64 * i + lane];
-    auto vt_operand = [&](int t) __attribute__((always_inline)) {
-      const int vo = 128 * (t >> 1) + 2 * lane + (t & 1);  // in 8-byte units
-      const uint2 va = reinterpret_cast<const uint2*>(st[2])[vo];
-      const uint2 vb = reinterpret_cast<const uint2*>(st[3])[vo];
-      return make_uint4(va.x, va.y, vb.x, vb.y);
-    };
-    uint4 vf[NQ > 1 ? NT : 1];
-    if constexpr (NQ > 1) {
+      for (int r = 0; r < 4; ++r) e[pg][r] = fmaf(sv[pg][r], qscale, -m);
+    const float top = fmaxf(fmaxf(fmaxf(e[0][0], e[0][1]), fmaxf(fmaxf(e[0][2], e[0][3]), e[1][0])),
+                            fmaxf(fmaxf(e[1][1], e[1][2]), e[1][3]));
+    if (__any(top > 8.f)) {
+      float mp = fmaxf(fmaxf(fmaxf(sv[0][0], sv[0][1]), fmaxf(sv[0][2], sv[0][3])),
+                       fmaxf(fmaxf(sv[1][0], sv[1][1]), fmaxf(sv[1][2], sv[1][3])));
+      mp = max_xor32(max_xor16(mp)) * qscale;  // in log2 units
+      const float mn = fmaxf(m, mp);
+      const float corr = exp2f(m - mn);
+      m = mn;
+      l *= corr;
 #pragma unroll
-      for (int t = 0; t < NT; ++t) vf[t] = vt_operand(t);
+      for (int t = 0; t < NT; ++t) o[t] *= corr;
+#pragma unroll
+      for (int pg = 0; pg < 2; ++pg)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) e[pg][r] = fmaf(sv[pg][r], qscale, -m);
     }
-
-    // keys of this pair visible to every query of the block: no mask needed
-    const bool all_visible = (2 * pair + 2) * kPage - 1 <= first_pos;
+    float pv[2][4];
+    float ps = 0.f;
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-      float sv[2][4];  // raw scores q.k
+    for (int pg = 0; pg < 2; ++pg)
 #pragma unroll
-      for (int pg = 0; pg < 2; ++pg) {
-        f32x4 sc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < KQ; ++i) sc = mfma_k32(kf[pg][i], qf[n][i], sc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sv[pg][r] = sc[r];
+      for (int r = 0; r < 4; ++r) {
+        pv[pg][r] = exp2_hw(e[pg][r]);
+        ps += pv[pg][r];
       }
-      if (!all_visible) {
+    l += ps;
+    // P^T operand over the page pair: k-slot 8grp+j is key 4grp+j of page
+    // j/4, the order of the V^T operand
+    uint4 hi, lo;
+    split_bf16(pv[0][0], pv[0][1], hi.x, lo.x);
+    split_bf16(pv[0][2], pv[0][3], hi.y, lo.y);
+    split_bf16(pv[1][0], pv[1][1], hi.z, lo.z);
+    split_bf16(pv[1][2], pv[1][3], hi.w, lo.w);
+    // V^T operands of output tiles 2c, 2c + 1 over the pair, keys 4grp ..
+    // 4grp+3 of each page: a page's 16 bytes hold both tiles', so their inner
+    // halves trade places (those of c + 1 between the MFMAs of c)
+    uint4 v[2][2];
+    v[0][0] = st[2][lane];
+    v[0][1] = st[3][lane];
+    swap_halves<2>(v[0][0], v[0][1]);
 #pragma unroll
-        for (int pg = 0; pg < 2; ++pg)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if ((2 * pair + pg) * kPage + 4 * grp + r > qpos[n]) sv[pg][r] = -INFINITY;
+    for (int c = 0; c < NT / 2; ++c) {
+      uint4(&cur)[2] = v[c & 1], (&next)[2] = v[(c + 1) & 1];
+      if (c + 1 < NT / 2) {
+        next[0] = st[2][64 * (c + 1) + lane];
+        next[1] = st[3][64 * (c + 1) + lane];
       }
-      // The reference max m only moves when some column's max exceeds it by
-      // more than 8 (a factor 2^8): o and l carry the same scale, so their
-      // quotient is unchanged, and p = 2^(s - m) stays below 2^8.  Whether any
-      // score does is read off the exponents s*scale - m themselves, so the
-      // column maxima (a cross-lane reduction) are formed only when m moves.
-      float e[2][4];
-      bool grow = false;
-#pragma unroll
-      for (int pg = 0; pg < 2; ++pg)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          e[pg][r] = fmaf(sv[pg][r], qscale, -m[n]);
-          grow |= e[pg][r] > 8.f;
-        }
-      if (__any(grow)) {
-        float mp = fmaxf(fmaxf(fmaxf(sv[0][0], sv[0][1]), fmaxf(sv[0][2], sv[0][3])),
-                         fmaxf(fmaxf(sv[1][0], sv[1][1]), fmaxf(sv[1][2], sv[1][3])));
-        mp = max_xor32(max_xor16(mp)) * qscale;  // in log2 units
-        const float mn = fmaxf(m[n], mp);
-        const float corr = exp2f(m[n] - mn);
-        m[n] = mn;
-        l[n] *= corr;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) o[n][t] *= corr;
-#pragma unroll
-        for (int pg = 0; pg < 2; ++pg)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) e[pg][r] = fmaf(sv[pg][r], qscale, -m[n]);
-      }
-      float pv[2][4];
-      float ps = 0.f;
-#pragma unroll
-      for (int pg = 0; pg < 2; ++pg)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          pv[pg][r] = exp2_hw(e[pg][r]);
-          ps += pv[pg][r];
-        }
-      l[n] += ps;
-      // P^T operand over the page pair: k-slot 8grp+j is key 4grp+j of page
-      // j/4, the order of the V^T operand
-      uint4 hi, lo;
-      split_bf16(pv[0][0], pv[0][1], hi.x, lo.x);
-      split_bf16(pv[0][2], pv[0][3], hi.y, lo.y);
-      split_bf16(pv[1][0], pv[1][1], hi.z, lo.z);
-      split_bf16(pv[1][2], pv[1][3], hi.w, lo.w);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const uint4 v = NQ > 1 ? vf[NQ > 1 ? t : 0] : vt_operand(t);
-        o[n][t] = mfma_k32(v, hi, o[n][t]);
-        o[n][t] = mfma_k32(v, lo, o[n][t]);
-      }
+      o[2 * c] = mfma_k32(cur[0], hi, o[2 * c]);
+      o[2 * c + 1] = mfma_k32(cur[1], hi, o[2 * c + 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (c + 1 < NT / 2) swap_halves<0>(next[0], next[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      o[2 * c] = mfma_k32(cur[0], lo, o[2 * c]);
+      o[2 * c + 1] = mfma_k32(cur[1], lo, o[2 * c + 1]);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
+  const float L = sum_xor32(sum_xor16(l));
+  if (!qok) return;
+  const float inv = 1.0f / L;
+  uint16_t* op = a.out + (static_cast<size_t>(qrow) * a.nq + h * G + col % G) * HD;
 #pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    const float L = sum_xor32(sum_xor16(l[n]));
-    if (!qok[n]) continue;
-    const float inv = 1.0f / L;
-    uint16_t* op = a.out + (static_cast<size_t>(qrow[n]) * a.nq + h * G + col % G) * HD;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      uint2 w;
-      w.x = pack_bf16x2(o[n][t][0] * inv, o[n][t][1] * inv);
-      w.y = pack_bf16x2(o[n][t][2] * inv, o[n][t][3] * inv);
-      *reinterpret_cast<uint2*>(op + 16 * t + 4 * grp) = w;
-    }
+  for (int t = 0; t < NT; ++t) {
+    uint2 w;
+    w.x = pack_bf16x2(o[t][0] * inv, o[t][1] * inv);
+    w.y = pack_bf16x2(o[t][2] * inv, o[t][3] * inv);
+    *reinterpret_cast<uint2*>(op + 16 * t + 4 * grp) = w;
   }
 }
 
@@ -560,12 +554,12 @@ hipError_t launch_attn_decode(const AttnArgs& a, hipStream_t s) {
 
 template <int HD>
 static hipError_t launch_prefill_hd(const PrefillAttnArgs& a, hipStream_t s) {
-  const dim3 grid(a.n_blocks * a.nkv), block(PrefillShape<HD>::NW * 64);
+  const dim3 grid(a.n_blocks * a.nkv), block(kPrefillWaves * 64);
   switch (a.nq / a.nkv) {
-    case 1: launch_kernel((attn_prefill_kernel<HD, 1, PrefillShape<HD>::NW, PrefillShape<HD>::NQ>), grid, block, 0, s, a); break;
-    case 2: launch_kernel((attn_prefill_kernel<HD, 2, PrefillShape<HD>::NW, PrefillShape<HD>::NQ>), grid, block, 0, s, a); break;
-    case 4: launch_kernel((attn_prefill_kernel<HD, 4, PrefillShape<HD>::NW, PrefillShape<HD>::NQ>), grid, block, 0, s, a); break;
-    case 8: launch_kernel((attn_prefill_kernel<HD, 8, PrefillShape<HD>::NW, PrefillShape<HD>::NQ>), grid, block, 0, s, a); break;
+    case 1: launch_kernel((attn_prefill_kernel<HD, 1>), grid, block, 0, s, a); break;
+    case 2: launch_kernel((attn_prefill_kernel<HD, 2>), grid, block, 0, s, a); break;
+    case 4: launch_kernel((attn_prefill_kernel<HD, 4>), grid, block, 0, s, a); break;
+    case 8: launch_kernel((attn_prefill_kernel<HD, 8>), grid, block, 0, s, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -578,6 +572,6 @@ hipError_t launch_attn_prefill(const PrefillAttnArgs& a, hipStream_t s) {
   return hipErrorInvalidValue;
 }
 
-int prefill_tokens_per_block(int group) { return kPrefillTilesPerBlock * 16 / group; }
+int prefill_tokens_per_block(int group) { return kPrefillWaves * 16 / group; }
 
 }  // namespace metro

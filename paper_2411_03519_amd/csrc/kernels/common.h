@@ -116,10 +116,10 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-// 16 bytes per lane from gptr into LDS bytes lds_base + 16 * lane; one wait
-// state separates the M0 write from the load that reads it
-__device__ __forceinline__ void lds_load16(const void* gptr, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_base)
+// 16 bytes per lane from base + off (base wave-uniform) into LDS bytes lds_base
+// + 16 * lane; one wait state separates the M0 write from the load that reads it
+__device__ __forceinline__ void lds_load16s(const void* base, uint32_t off, uint32_t lds_base) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base)
                : "memory", "m0");
 }
 

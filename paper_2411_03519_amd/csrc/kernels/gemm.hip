@@ -338,12 +338,6 @@ __device__ __forceinline__ int xcd_contiguous(int b, int total) {
   return x * q + min(x, r) + s;
 }
 
-// 16 bytes per lane from base + off (base wave-uniform) into LDS
-__device__ __forceinline__ void lds_load16s(const void* base, uint32_t off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base)
-               : "memory", "m0");
-}
-
 // c += a . b with the accumulator held in place in AGPRs: 64 of these fill the
 // AGPR half of the register file, and left to itself the compiler's register
 // allocation moves them about inside the loop (430 moves per 128 MFMAs).  The

@@ -209,6 +209,19 @@ def test_prefill_attention_llama_shapes(metro, G):
     compare(gots, rows, kv, G, f"prefill 8 kv heads group {G}")
 
 
+@pytest.mark.parametrize("hd,G", [(128, 4), (64, 2), (128, 1)])
+def test_prefill_attention_block_and_page_id_edges(metro, hd, G):
+    # chunks around one and two query blocks (128 / G rows each), ending around
+    # 64 and 128 page pairs (2048 and 4096 keys: the page ids of 64 pairs are
+    # read at a time)
+    rng = np.random.default_rng(600 + hd + G)
+    n = 128 // G
+    items = [(2048 - n, n, True), (2049 - n, n, False), (2080 - n - 1, n + 1, True), (4096 - 2 * n, 2 * n, False),
+             (4097 - n, n - 1, True), (0, 2 * n + 1, False)]
+    gots, rows, kv = run_prefill(metro, rng, hd, G, 2, items)
+    compare(gots, rows, kv, G, f"prefill block edges hd {hd} group {G}")
+
+
 def test_attention_ops_reject_bad_arguments(metro):
     q = torch.zeros(64 * 128, dtype=torch.int16, device="cuda")
     kv = torch.zeros(4 * 2 * 8 * 16 * 128, dtype=torch.int16, device="cuda")
