@@ -356,7 +356,7 @@ __global__ __launch_bounds__(kPrefillWaves * 64, 4) void attn_prefill_kernel(Pre
 
   // this lane's query column
   const int tok = wave * TPW + col / G;
-  const bool qok = tok < nrows;
+  const bool qok = tok < nrows, active = wave * TPW < nrows;
   const int qrow = row0 + (qok ? tok : 0);
   const int qpos = qok ? a.pos[qrow] : -1;
   uint4 qf[KQ];
@@ -414,6 +414,10 @@ __global__ __launch_bounds__(kPrefillWaves * 64, 4) void attn_prefill_kernel(Pre
       __syncthreads();
     }
 
+    // Waves without a row of the block (a one-token item beside the chunks of a
+    // mixed forward has one row, a ragged chunk's last block a few) only bring
+    // their parts of the pages.
+    if (!active) continue;
     // scores q.k, K operand (A of S^T): key row col, dims 32i + 8grp .. +7
     float sv[2][4];
 #pragma unroll

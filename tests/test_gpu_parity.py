@@ -188,6 +188,35 @@ def test_mixed_prefill_and_decode_items(metro, tiny_case):
     assert_logits_close(last[1][None, None], gens[3][1][None, :1], "mixed seq 3")
 
 
+@pytest.mark.parametrize("only_single", [False, True])
+def test_one_token_items_match_decode_steps(metro, only_single):
+    """One-token items of a prefill call leave all but one wave of their query
+    block idle: their logits beside other items, or alone, are those of a
+    decode step on the same context, up to the fp32 rounding of other sum
+    orders (bounded as the oracle comparison is)."""
+    w = synth.llama_weights(synth.TINY, 3)
+    rng = np.random.default_rng(31)
+    ctx = [2047, 2048, 16, 4500, 1, 300]
+    with make_model(metro, synth.TINY, w, max_batch=16, max_tokens=8192, max_context=4608, max_seqs=32) as m:
+        V = m.vocab
+        base = [m.seq_open() for _ in ctx]
+        for s, n in zip(base, ctx):
+            m.prefill_chunk([s], [rng.integers(0, V, n)])
+        toks = rng.integers(0, V, len(ctx)).astype(np.int32)
+        forks = [m.seq_fork(s, n) for s, n in zip(base, ctx)]
+        want = torch.empty(len(ctx), V, device="cuda")
+        m.decode_step(forks, toks, want)
+        seqs, chunks = list(base), [[t] for t in toks]
+        if not only_single:
+            seqs[3:3] = [m.seq_open(), m.seq_open()]
+            chunks[3:3] = [rng.integers(0, V, 70), rng.integers(0, V, 2)]
+        got = torch.empty(len(seqs), V, device="cuda")
+        m.prefill_chunk(seqs, chunks, got)
+        keep = [i for i, c in enumerate(chunks) if len(c) == 1]
+        assert len(keep) == len(ctx)
+        assert (got[keep] - want).abs().max().item() <= 2e-2
+
+
 def test_decode_rows_independent_of_batch_composition(metro):
     w = synth.llama_weights(synth.TINY, 1)
     rng = np.random.default_rng(21)
