@@ -309,6 +309,14 @@ struct TileShape {
 using BigTile = TileShape<8, 8>;
 using MidTile = TileShape<4, 4>;
 using WideTile = TileShape<8, 4>;
+// Small: 33 to 64 rows.  The decode kernel's waves each read the activations of
+// their k blocks from L2, at 64 rows as many bytes as the weights; here the
+// four waves share them through LDS.  Us at M = 40 / 64, decode kernel -> this:
+// 8B QKV 21.8 / 26.0 -> 16.2 / 16.7, O 15.8 / 18.7 -> 13.6 / 14.5, gate/up 47.9 /
+// 49.3 -> 43.3 / 43.6, down 30.6 / 34.3 -> 27.6 / 28.0, LM head 213 / 240 -> 195 /
+// 207; 70B QKV 51.9 / 60.4 -> 40.3 / 41.9.  At 25 and 32 rows the two are within
+// 4% (8B O 12.4 against 12.9), and the decode kernel keeps those.
+using SmallTile = TileShape<4, 2>;
 
 // Grouped tile order: consecutive tiles sweep groups of kGroupM m-tiles, m
 // fastest within a group, so that the blocks in flight cover a compact patch of
@@ -768,6 +776,13 @@ static int skinny_tiles(int N, int Kp, int epilogue) {
   return N <= 8192 && Kp <= 4096 ? 2 : 4;
 }
 
+// Whether a decode-sized product takes the Small tile: from 33 rows on, unless
+// the weights are too few (4M, i.e. 8 MB) for the activation reads to matter:
+// there both are bound by latency, and the decode kernel needs one launch.
+static bool takes_small_tile(int M, int N, int Kp) {
+  return M > kSkinnyMaxRows && static_cast<int64_t>(N) * Kp >= (1 << 22);
+}
+
 // Decode kernel: workgroups split K while fewer than `target` cover the
 // product; slices stay multiples of 128, and the slice sums (ks * M * N fp32,
 // written and read again) stay within a quarter of the weight bytes (N * Kp
@@ -807,7 +822,8 @@ static int device_cus() {
 }
 
 // Kernel choice, from probes over M = 80 .. 12800 at the Llama-3-8B and 70B
-// shapes: the decode kernel up to 64 rows; then 128 x 128 tiles (more blocks)
+// shapes: decode batches (up to 64 rows) the decode kernel or the Small tile
+// (takes_small_tile); then 128 x 128 tiles (more blocks)
 // for narrow products, and for wide ones up to 192 rows while their tiles
 // number at most the CUs (in the 70B model at M=128 gate/up took 242 us as 448
 // such tiles against 203 us as 224 of 256 x 256, although cache-cold probes
@@ -821,8 +837,11 @@ GemmPlan plan_gemm(int M, int N, int Kp, int epilogue, int64_t part_cap) {
   const bool split = can_split && epilogue != kEpiSwiGLU && M <= kSplitMaxRows;
   if (M <= 64) {
     p.kind = GemmKind::kSkinny;
-    p.nt = skinny_tiles(N, Kp, epilogue);
-    if (split) p.ks = gemm_k_splits(N / (16 * p.nt), p.nt == 2 ? 512 : 256, M, Kp);
+    p.nt = takes_small_tile(M, N, Kp) ? 0 : skinny_tiles(N, Kp, epilogue);
+    if (split && p.nt == 0)
+      p.ks = tiled_k_splits((N + SmallTile::BN - 1) / SmallTile::BN, device_cus(), M, Kp);
+    else if (split)
+      p.ks = gemm_k_splits(N / (16 * p.nt), p.nt == 2 ? 512 : 256, M, Kp);
     while (p.ks > 1 && static_cast<int64_t>(p.ks) * M * N > part_cap) p.ks /= 2;
     return p;
   }
@@ -936,7 +955,9 @@ static hipError_t launch_epi(const GemmPlan& p, const uint16_t* X, int ldx, cons
                              float* outf, uint16_t* outb, int ldo, float* part, hipStream_t s) {
   switch (p.kind) {
     case GemmKind::kSkinny:
-      if (p.nt == 7)
+      if (p.nt == 0)
+        launch_tiled<SmallTile, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
+      else if (p.nt == 7)
         launch_skinny_m<7, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
       else if (p.nt == 4)
         launch_skinny_m<4, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
@@ -990,7 +1011,7 @@ hipError_t launch_gemm(const uint16_t* X, int ldx, const uint16_t* W, int Kp, in
 // (with 4 k slices the product alone takes 13.1 us, but the slice sums then
 // cost a RoPE kernel of 5.2 us)
 bool gemm_rope_kv_fused(int M, int N, int Kp) {
-  return M <= kRopeKVMaxRows || plan_gemm(M, N, Kp, kEpiStoreF32, 0).kind == GemmKind::kBig;
+  return (M <= kRopeKVMaxRows && !takes_small_tile(M, N, Kp)) || plan_gemm(M, N, Kp, kEpiStoreF32, 0).kind == GemmKind::kBig;
 }
 
 hipError_t launch_gemm_rope_kv(const uint16_t* X, int ldx, const uint16_t* W, int Kp, int M, int N, const RopeKV& rk,

@@ -138,19 +138,20 @@ struct RopeKV {
 // one with 256-row tiles (any epilogue) may split only the tiles of its last,
 // partly filled round (up to CUs * 256 * 256 floats of part), and completes
 // them itself (*n_parts stays 0).
-// Kernel choice (plan_gemm): up to 64 rows the weight-streaming decode GEMM;
-// then the tiled GEMM with 128 x 128 blocks (narrow products up to
+// Kernel choice (plan_gemm): up to 64 rows the decode kind (weight streaming, or
+// 128 x 64 tiles for large products of 33 rows and more); then the tiled GEMM with 128 x 128 blocks (narrow products up to
 // kMidMaxRows rows, wide ones while they fit the CUs), 256 (W rows) x 128
 // blocks (wide products at up to 256 rows otherwise, narrow ones of up to 128
 // rows that 128 x 128 blocks would leave mostly idle), or 256 x 256 blocks.
 enum class GemmKind { kSkinny, kMid, kWide, kBig };
 struct GemmPlan {
   GemmKind kind;
-  int nt;          // row tiles per wave (decode kernel)
+  int nt;          // row tiles per wave (decode kernel; 0: 128 x 64 tiles)
   int ks;          // k slices of every tile
   int tail_split;  // k slices of each tile from tail_first on (1: none)
   int tail_first;
 };
+constexpr int kSkinnyMaxRows = 32;  // rows up to which every product streams its weights
 constexpr int kMidMaxRows = 1000;
 constexpr int kSplitMaxRows = 1024;
 GemmPlan plan_gemm(int M, int N, int Kp, int epilogue, int64_t part_cap);
@@ -159,7 +160,9 @@ hipError_t launch_gemm(const uint16_t* X, int ldx, const uint16_t* W, int Kp, in
                        hipStream_t s);
 // QKV projection (N = (nq + 2 nkv) * hd) with RoPE and the KV cache write in
 // its epilogue, in place of launch_gemm + launch_rope_kv, for the shapes
-// gemm_rope_kv_fused accepts: up to kRopeKVMaxRows rows (decode kernel), or
+// gemm_rope_kv_fused accepts: up to kRopeKVMaxRows rows (decode kernel; not
+// where 128 x 64 tiles with k slices and the RoPE kernel cost less: 8B at M = 64
+// 26 against 16.7 + 5.4 us), or
 // the batches plan_gemm gives 256 x 256 tiles (prefill chunks); K is not split,
 // so no slice sums are left.  hipErrorInvalidValue for other shapes.
 constexpr int kRopeKVMaxRows = 64;

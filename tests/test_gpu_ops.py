@@ -262,11 +262,13 @@ def test_gemm_repeated_launches_are_bitwise_stable(metro):
                 np.testing.assert_array_equal(got, first[i], err_msg=f"case {c[:5]} launch {rep}")
 
 
-# Row blocks of the tiled kernel are evened out over the rows (32 TM rows, TM 3
-# or 4 for 128-row blocks, 5 .. 8 for 256-row ones): both sides of each step,
-# with a last block that is nearly empty, ragged N, and k slices / a split last
-# round when given a workspace.
-EVEN_ROWS = [(96, 1056), (97, 1056), (192, 160), (193, 16384), (192, 28672), (257, 16416), (320, 16384), (321, 16384),
+# Row blocks of the tiled kernel: 64 rows from 33 to 64 rows on for products of
+# 4M weights and more; above, evened out over the rows (32 TM rows, TM 3 or 4 for
+# 128-row blocks, 5 .. 8 for 256-row ones).  Both sides of each step, with a last
+# block that is nearly empty, ragged N, and k slices / a split last round when
+# given a workspace.
+EVEN_ROWS = [(32, 16384), (33, 16384), (48, 11008), (64, 28672), (64, 1056), (96, 1056), (97, 1056), (192, 160), (193, 16384), (192, 28672),
+             (257, 16416), (320, 16384), (321, 16384),
              (385, 16384), (449, 16384), (513, 16384), (1001, 288), (1025, 288), (1281, 160)]
 
 
