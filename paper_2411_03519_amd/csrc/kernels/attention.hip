@@ -277,14 +277,23 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(AttnArgs a) {
   const int w0 = a.row_work[row];
   const int d = threadIdx.x;
   auto state = [&](int s2) { return a.part + ((static_cast<size_t>(w0 + s2) * a.nkv + h) * G + g) * (hd + 2); };
+  // Lane l brings split l's max and sum (64 splits at a time), so that neither
+  // the maximum nor the weights wait on one memory round trip per split (rows of
+  // 2..15 splits, 192 blocks: 111.5 -> 108.8 us for the whole call).
+  const int lane = threadIdx.x & 63;
   float M = kNegBig;
-  for (int s2 = 0; s2 < ns; ++s2) M = fmaxf(M, state(s2)[hd]);
+  for (int s0 = 0; s0 < ns; s0 += 64) M = fmaxf(M, wave_max(s0 + lane < ns ? state(s0 + lane)[hd] : kNegBig));
   float L = 0.f, O = 0.f;
-  for (int s2 = 0; s2 < ns; ++s2) {
-    const float* pp = state(s2);
-    const float f = exp2f(pp[hd] - M);
-    L += pp[hd + 1] * f;
-    O += pp[d] * f;
+  for (int s0 = 0; s0 < ns; s0 += 64) {
+    const int n = min(64, ns - s0);
+    const float* mine = state(s0 + min(lane, n - 1));
+    const float f = exp2f(mine[hd] - M), lf = mine[hd + 1];
+#pragma unroll 4
+    for (int s2 = 0; s2 < n; ++s2) {
+      const float fs = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), s2));
+      L += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lf), s2)) * fs;
+      O += state(s0 + s2)[d] * fs;
+    }
   }
   a.out[(static_cast<size_t>(a.row_qrow[row]) * a.nq + j) * hd + d] = f32_to_bf16(O / L);
 }

@@ -422,24 +422,45 @@ metro_status scratch_on_current_device(void** out) {
 // Descriptor arrays of decode attention built on the device from the rows'
 // context lengths, in the order and with the values the host builds them for
 // metro_op_attn_decode (row i's pages at the running page offset, its work
-// items at the running work offset, splits of decode_splits()).  One thread:
-// a few hundred cycles per row.
-__global__ void describe_decode_kernel(const int32_t* ctx, int rows, int32_t* row_q, int32_t* row_bt,
-                                       int32_t* row_work, int32_t* row_nsplit, int32_t* work) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int32_t bo = 0, w = 0;
-  for (int i = 0; i < rows; ++i) {
-    const int32_t np = (ctx[i] + 15) / 16;
+// items at the running work offset, splits of decode_splits()).  One workgroup,
+// a thread per row of each run of kDescribeRows: both running offsets are a scan
+// of the run (one thread over all rows took a few hundred cycles per row: the
+// whole call at 256 rows of 226..339 keys 131 -> 85 us, of 1000..3000 444 -> 394).
+constexpr int kDescribeRows = 256;
+
+__global__ __launch_bounds__(kDescribeRows) void describe_decode_kernel(const int32_t* ctx, int rows, int32_t* row_q,
+                                                                        int32_t* row_bt, int32_t* row_work,
+                                                                        int32_t* row_nsplit, int32_t* work) {
+  __shared__ int2 sum[kDescribeRows];
+  const int t = threadIdx.x;
+  int32_t bo = 0, w0 = 0;
+  for (int r0 = 0; r0 < rows; r0 += kDescribeRows) {
+    const int i = r0 + t;
+    const int32_t np = i < rows ? (ctx[i] + 15) / 16 : 0;
     const int32_t ns = (np + metro::kDecodePagesPerSplit - 1) / metro::kDecodePagesPerSplit;
-    row_q[i] = i;
-    row_bt[i] = bo;
-    row_work[i] = w;
-    row_nsplit[i] = ns;
-    for (int sp = 0; sp < ns; ++sp, ++w) {
-      work[2 * w] = i;
-      work[2 * w + 1] = sp;
+    sum[t] = make_int2(np, ns);
+    __syncthreads();
+    for (int o = 1; o < kDescribeRows; o *= 2) {
+      const int2 add = t >= o ? sum[t - o] : make_int2(0, 0);
+      __syncthreads();
+      sum[t].x += add.x;
+      sum[t].y += add.y;
+      __syncthreads();
     }
-    bo += np;
+    if (i < rows) {
+      const int32_t w = w0 + sum[t].y - ns;
+      row_q[i] = i;
+      row_bt[i] = bo + sum[t].x - np;
+      row_work[i] = w;
+      row_nsplit[i] = ns;
+      for (int sp = 0; sp < ns; ++sp) {
+        work[2 * (w + sp)] = i;
+        work[2 * (w + sp) + 1] = sp;
+      }
+    }
+    bo += sum[kDescribeRows - 1].x;
+    w0 += sum[kDescribeRows - 1].y;
+    __syncthreads();
   }
 }
 
@@ -1208,7 +1229,7 @@ metro_status metro_op_attn_decode_noalloc(const uint16_t* q, const uint16_t* kv,
   hipStream_t s = static_cast<hipStream_t>(stream);
   HIP_TRY(nullptr, hipMemcpyAsync(d_ctx, ctx, rows * 4, hipMemcpyHostToDevice, s));
   HIP_TRY(nullptr, hipMemcpyAsync(d_bt, block_tables, pages * 4, hipMemcpyHostToDevice, s));
-  hipLaunchKernelGGL(describe_decode_kernel, dim3(1), dim3(64), 0, s, d_ctx, rows, d_q, d_bto, d_work0, d_ns,
+  hipLaunchKernelGGL(describe_decode_kernel, dim3(1), dim3(kDescribeRows), 0, s, d_ctx, rows, d_q, d_bto, d_work0, d_ns,
                      d_work);
   HIP_TRY(nullptr, hipGetLastError());
   metro::AttnArgs a{};

@@ -64,6 +64,18 @@ def test_noalloc_decode_matches_allocating_entry_point_twice(metro):
     case(metro, rng, 64, 2, 2, [1, 17, 300, 2049, 5, 64, 33])
 
 
+@pytest.mark.parametrize("rows", [1, 255, 256, 257, 520])
+def test_noalloc_descriptors_across_runs_of_rows(metro, rows):
+    # the work list is built 256 rows at a time; a few rows of several work items
+    # (one of more than 64) make its running offsets differ from the row number
+    rng = np.random.default_rng(910 + rows)
+    ctxs = rng.integers(1, 40, rows)
+    ctxs[[0, rows // 2, rows - 1]] = [2049, 4097, 6200]
+    if rows == 1:
+        ctxs[0] = 66 * 2048 + 5
+    case(metro, rng, 64, 2, 1, list(ctxs))
+
+
 def test_noalloc_decode_rejects_what_exceeds_the_array(metro):
     rows, ctx = 20000, 4096                          # ~670 MB of split states
     q = torch.zeros(64, dtype=torch.int16, device="cuda")
