@@ -332,9 +332,9 @@ __device__ __attribute__((noinline)) void zero_v_past(uint32_t* vt, int n0, int 
 // Blocks run last rows first: those see the most keys, and the short ones fill
 // the end of the launch.
 // Measured (nq 32, nkv 8, hd 128; us, before -> now): chunks of 3500 and 3800
-// after 2000 and 8000 keys 1450 -> 1237; 25 prompts of 256 .. 2416 862 -> 699;
-// one of 2048 94 -> 67; 161 rows after 448 keys 29.6 -> 20.2; hd 64, 3 x 700
-// after 1000 81 -> 60.
+// after 2000 and 8000 keys 1456 -> 1317; 25 prompts of 256 .. 2416 890 -> 726;
+// one of 2048 96 -> 72; 161 rows after 448 keys 29.7 -> 20.3; hd 64, 3 x 700
+// after 1000 83 -> 64.
 constexpr int kPrefillWaves = 8;
 
 template <int HD, int G>

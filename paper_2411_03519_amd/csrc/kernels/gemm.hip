@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restri
 
 // ---------------------------------------------------------------------------
 // Tiled GEMM of 4 waves, one per SIMD (2 x 2, each 16 TN rows of W x 16 TM
-// activation rows of v_mfma_f32_16x16x32_bf16), for more than 64 rows.
+// activation rows of v_mfma_f32_16x16x32_bf16), for more than 32 rows.
 //
 // What bounds it: for prefill chunks the chip's power limit, which it reaches
 // with random operands, so the energy per flop counts as much as the stalls;

@@ -50,5 +50,14 @@ def test_accumulators_stay_in_place(kernels):
             if i < mfma[0]:
                 r = int(re.match(r"v_accvgpr_write_b32 a(\d+), 0$", ops[i]).group(1))
                 assert first[r] - i >= 4, (name, ops[i])
+        # no vector instruction writes an operand of one of the next two MFMAs' slots (2 wait states)
+        for i in range(mfma[0], mfma[-1]):
+            d = re.match(r"(?!v_mfma)v_\w+ v(?:\[(\d+):(\d+)\]|(\d+))", ops[i])
+            if not d:
+                continue
+            lo, hi = int(d.group(1) or d.group(3)), int(d.group(2) or d.group(3))
+            for ln in ops[i + 1:i + 3]:
+                for a, b in re.findall(r" v\[(\d+):(\d+)\]", ln) if ln.startswith("v_mfma") else ():
+                    assert hi < int(a) or lo > int(b), (name, ops[i], ln)
         after = min(i for i in agpr if i > mfma[-1])
         assert "s_nop 7" in ops[mfma[-1] + 1:after], (name, ops[mfma[-1]:after + 1])
