@@ -318,20 +318,54 @@ using WideTile = TileShape<8, 4>;
 // 4% (8B O 12.4 against 12.9), and the decode kernel keeps those.
 using SmallTile = TileShape<4, 2>;
 
-// Grouped tile order: consecutive tiles sweep groups of kGroupM m-tiles, m
-// fastest within a group, so that the blocks in flight cover a compact patch of
-// tiles and share their W and X tiles through the caches (256 x 256 tiles: 32
-// consecutive ones, the CUs of one XCD, cover 4 x 8).
+// Grouped tile order: consecutive tiles sweep groups of GM m-tiles, m fastest
+// within a group, so that the blocks in flight cover a compact patch of tiles
+// and share their W and X tiles through the caches.  256-row tiles are visited
+// in groups of 4 (32 consecutive 256 x 256 tiles, the CUs of one XCD, cover 4 x
+// 8); all others, and the tiles of a last round that is cut in k slices, are
+// counted in groups of 16.
+constexpr int kTailGroupM = 16;
 template <class S>
-__host__ __device__ __forceinline__ void tile_origin(int t, int M, int N, int& m0, int& n0) {
-  constexpr int kGroupM = S::TN * S::TM > 32 ? 4 : 16;
+constexpr int kGroupM = S::TN * S::TM > 32 ? 4 : kTailGroupM;
+
+template <class S, int GM>
+__device__ __forceinline__ void tile_origin(int t, int M, int N, int& m0, int& n0) {
   const int mt = (M + S::BM - 1) / S::BM, nt = (N + S::BN - 1) / S::BN;
-  const int group = t / (kGroupM * nt);
-  const int first_m = group * kGroupM;
-  const int gm = min(mt - first_m, kGroupM);
-  const int in = t % (kGroupM * nt);
+  const int group = t / (GM * nt);
+  const int first_m = group * GM;
+  const int gm = min(mt - first_m, GM);
+  const int in = t % (GM * nt);
   n0 = (in / gm) * S::BN;
   m0 = (first_m + in % gm) * S::BM;
+}
+
+// Tile t of the first `full` tiles in the order of groups of 16, visited in the
+// kernel's own order.  Which tiles the last round cuts in k slices decides how
+// their fp32 sums are grouped, so that set does not follow the order in which
+// the others are visited.  A whole group of 16 holds four whole groups of 4; of
+// the group that the last round cuts, the first rows may have one column more.
+template <class S>
+__device__ __forceinline__ void full_tile_origin(int t, int full, int M, int N, int& m0, int& n0) {
+  constexpr int GM = kGroupM<S>;
+  const int mt = (M + S::BM - 1) / S::BM, nt = (N + S::BN - 1) / S::BN;
+  const int whole = full / (kTailGroupM * nt), first = whole * kTailGroupM * nt;
+  if (GM == kTailGroupM || t < first) {
+    tile_origin<S, GM>(t, M, N, m0, n0);
+    return;
+  }
+  const int h = min(mt - whole * kTailGroupM, kTailGroupM);
+  const int cols = (full - first) / h, more = (full - first) % h;
+  t -= first;
+  int r = 0, gm = min(h, GM);
+  for (;;) {
+    const int n = gm * cols + min(max(more - r, 0), gm);
+    if (t < n || r + gm >= h) break;
+    t -= n;
+    r += gm;
+    gm = min(h - r, GM);
+  }
+  n0 = (t / gm) * S::BN;
+  m0 = (whole * kTailGroupM + r + t % gm) * S::BM;
 }
 
 // Workgroups are handed to the 8 XCDs in turn (workgroup b to XCD b % 8), and
@@ -507,11 +541,12 @@ constexpr int load_behind(int u, int nm, int nd) {
 
 // Work of one workgroup.  Without a tail split the grid's tiles x k slices
 // (slice-major list, tiles in tile_origin order) are spread over the XCDs by
-// xcd_contiguous.  With one (tail_split = S > 1), workgroups x < tail_first
-// take tile x over all of K, and the last tiles, which would leave most CUs
-// idle in the final round, are cut into S k slices each: workgroup tail_first +
-// u takes slice u % S of tile tail_first + u / S and stores its fp32 sums to
-// part[u][BM][BN] for gemm_tail_fixup_kernel.
+// xcd_contiguous.  With one (tail_split = S > 1), the last tiles in the order of
+// groups of 16, which would leave most CUs idle in the final round, are cut into
+// S k slices each: workgroup tail_first + u takes slice u % S of tile tail_first
+// + u / S and stores its fp32 sums to part[u][BM][BN] for
+// gemm_tail_fixup_kernel; workgroups x < tail_first take the other tiles over
+// all of K.
 // In tile_origin order 32 consecutive 256 x 256 tiles (one XCD's CUs) cover 4 x
 // 8 of them, so an XCD's L2 fetches 12 operand tiles per k step; the list in
 // grid order made that 18 (8B gate/up at M = 8192 1506 -> 1479 us).
@@ -528,23 +563,22 @@ __global__ __launch_bounds__(S::NTH, S::OCC) void gemm_tiled_kernel(const uint16
   const int wn = wave >> 1, wm = wave & 1;
   const int r16 = lane & 15, g = lane >> 4;
 
-  int tile = blockIdx.x, KS = gridDim.y, slice = blockIdx.y, unit = -1;
-  if (tail_split > 1 && tile >= tail_first) {
-    unit = tile - tail_first;
-    tile = tail_first + unit / tail_split;
+  int KS = gridDim.y, slice = blockIdx.y, unit = -1;
+  int m0, n0;
+  if (tail_split > 1 && static_cast<int>(blockIdx.x) >= tail_first) {
+    unit = blockIdx.x - tail_first;
     KS = tail_split;
     slice = unit % tail_split;
+    tile_origin<S, kTailGroupM>(tail_first + unit / tail_split, M, N, m0, n0);
   } else if (tail_split > 1) {
-    tile = xcd_contiguous(tile, tail_first);
+    full_tile_origin<S>(xcd_contiguous(blockIdx.x, tail_first), tail_first, M, N, m0, n0);
   } else {
     const int i = xcd_contiguous(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
     slice = i / gridDim.x;
-    tile = i % gridDim.x;
+    tile_origin<S, kGroupM<S>>(i % gridDim.x, M, N, m0, n0);
   }
   const int kspan = Kp / KS, k0 = slice * kspan;
   const int nc = kspan / 32;  // chunks (a multiple of 4)
-  int m0, n0;
-  tile_origin<S>(tile, M, N, m0, n0);
 
   // The wave's share of every W chunk (16-row tiles) and X stage (blocks of 8
   // rows).  Rows past N or M re-read the last valid row: finite values whose
@@ -706,7 +740,7 @@ __global__ __launch_bounds__(256) void gemm_tail_fixup_kernel(const float* __res
   const int i = blockIdx.y * (256 / kCols) + threadIdx.x / kCols;
   const int j = 4 * (threadIdx.x % kCols);
   int m0, n0;
-  tile_origin<S>(tail_first + blockIdx.x, M, N, m0, n0);
+  tile_origin<S, kTailGroupM>(tail_first + blockIdx.x, M, N, m0, n0);
   const int m = m0 + i, n = n0 + j;
   if (m >= M || n >= N) return;
   const float* p = part + static_cast<size_t>(blockIdx.x) * split * S::BM * S::BN + i * S::BN + j;
@@ -737,7 +771,7 @@ __global__ __launch_bounds__(256) void gemm_tail_fixup_swiglu_kernel(const float
   const int j = 4 * (threadIdx.x % kCols);
   const int wg = 16 * (j / 8) + j % 8;  // gate row of output column j within the tile
   int m0, n0;
-  tile_origin<S>(tail_first + blockIdx.x, M, N, m0, n0);
+  tile_origin<S, kTailGroupM>(tail_first + blockIdx.x, M, N, m0, n0);
   const int m = m0 + i;
   if (m >= M || n0 + wg >= N) return;
   const float* p = part + static_cast<size_t>(blockIdx.x) * split * S::BM * S::BN + i * S::BN + wg;

@@ -300,3 +300,39 @@ def test_gemm_even_row_blocks(metro, M, N, epi):
             metro.op_gemm(X, P, M, N, K, epi, out, N, workspace=ws)
             want, bound = ref + (init.double() if epi == 1 else 0.0), err
         assert bool(((out.double() - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(1500, 12288, 1024),    # 6 x 48 tiles of 256 x 256: the last 32
+                                   (576, 28672, 1024),     # 3 x 112 of 192 rows: the last 80
+                                   (2048, 12288, 1024),    # 8 x 48: the last 128
+                                   (4864, 4352, 1024),     # 19 x 17: the last 67, over two groups of 16 row tiles
+                                   (1717, 28672, 1024)])   # 7 x 112: the last 16 (8B gate/up)
+def test_gemm_last_round_is_the_same_tiles_in_any_visiting_order(metro, M, N, K):
+    """A last round of 256 x 256 tiles that is cut in k slices sums those tiles
+    in another order, so its tiles are fixed: the last ones in groups of 16 row
+    tiles, m fastest.  Every other tile has the bits of the uncut product."""
+    cus = 256
+    mt, nt = -(-M // 256), -(-N // 256)
+    cut = mt * nt % cus
+    print(f"last round M={M} N={N} K={K} cut={cut}", flush=True)
+    assert metro.op_gemm_plan(M, N, K, 0, True)[2] > 1
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    X = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
+    W = (0.05 * torch.randn(N, K, generator=g, device="cuda")).to(torch.bfloat16)
+    P = torch.empty_like(W)
+    metro.op_pack_weight(W, K, N, K, K, P)
+    outs = []
+    for ws in (None, torch.full((8, M, N), float("nan"), device="cuda")):
+        outs.append(torch.full((M, N), float("nan"), device="cuda"))
+        metro.op_gemm(X, P, M, N, K, 0, outs[-1], N, workspace=ws)
+    err = 1e-5 * (X.double().abs() @ W.double().abs().T) + 1e-6
+    assert bool(((outs[1].double() - X.double() @ W.double().T).abs() <= err).all())
+    rows = 32 * -(-(-(-M // mt)) // 32)  # rows of a tile: evened out over the row tiles
+    last = set()
+    for t in range(mt * nt - cut, mt * nt):
+        first = t // (16 * nt) * 16
+        gm, i = min(mt - first, 16), t % (16 * nt)
+        last.add((first + i % gm, i // gm))
+    differ = (outs[0] != outs[1]).nonzero()
+    got = {(m, n) for m, n in torch.unique(torch.stack([differ[:, 0] // rows, differ[:, 1] // 256], 1), dim=0).tolist()}
+    assert got == last
