@@ -1022,23 +1022,46 @@ static hipError_t launch_epi(const GemmPlan& p, const uint16_t* X, int ldx, cons
   return hipGetLastError();
 }
 
+// The tiled kernel reaches the rows of a block by 32-bit byte offsets from the
+// block's first element (they are 32 bits wide in the load itself).
+static bool offsets_fit(const GemmPlan& p, int M, int ldx, int Kp) {
+  if (p.kind == GemmKind::kSkinny && p.nt != 0) return true;  // 64-bit pointers
+  const bool big = p.kind == GemmKind::kBig, wide = p.kind == GemmKind::kWide, small = p.kind == GemmKind::kSkinny;
+  const int bn = big || wide ? BigTile::BN : MidTile::BN;
+  const int bm = big ? BigTile::BM : small ? SmallTile::BM : MidTile::BM;
+  constexpr int64_t kMax = int64_t{1} << 32;
+  return 2ll * ldx * std::min(M, bm) <= kMax && 2ll * Kp * bn <= kMax;
+}
+
 hipError_t launch_gemm(const uint16_t* X, int ldx, const uint16_t* W, int Kp, int M, int N, int epilogue,
                        float* out_f32, uint16_t* out_bf16, int ldo, float* part, int64_t part_cap, int* n_parts,
                        hipStream_t s) {
   *n_parts = 0;
   if (M <= 0) return hipSuccess;
+  auto run = [&](const GemmPlan& p, int m0, int rows) {
+    const uint16_t* x = X + static_cast<size_t>(m0) * ldx;
+    const size_t o = static_cast<size_t>(m0) * ldo;
+    switch (epilogue) {
+      case kEpiStoreF32:
+        return launch_epi<kEpiStoreF32>(p, x, ldx, W, Kp, rows, N, out_f32 + o, nullptr, ldo, part, s);
+      case kEpiAddF32:
+        return launch_epi<kEpiAddF32>(p, x, ldx, W, Kp, rows, N, out_f32 + o, nullptr, ldo, part, s);
+      case kEpiSwiGLU:
+        return launch_epi<kEpiSwiGLU>(p, x, ldx, W, Kp, rows, N, nullptr, out_bf16 + o, ldo, part, s);
+      default:
+        return hipErrorInvalidValue;
+    }
+  };
   const GemmPlan p = plan_gemm(M, N, Kp, epilogue, part != nullptr ? part_cap : 0);
-  if (p.ks > 1) *n_parts = p.ks;
-  switch (epilogue) {
-    case kEpiStoreF32:
-      return launch_epi<kEpiStoreF32>(p, X, ldx, W, Kp, M, N, out_f32, out_bf16, ldo, part, s);
-    case kEpiAddF32:
-      return launch_epi<kEpiAddF32>(p, X, ldx, W, Kp, M, N, out_f32, out_bf16, ldo, part, s);
-    case kEpiSwiGLU:
-      return launch_epi<kEpiSwiGLU>(p, X, ldx, W, Kp, M, N, out_f32, out_bf16, ldo, part, s);
-    default:
-      return hipErrorInvalidValue;
+  if (offsets_fit(p, M, ldx, Kp)) {
+    if (p.ks > 1) *n_parts = p.ks;
+    return run(p, 0, M);
   }
+  // rows millions of elements apart: the decode kernel, 64 rows at a time
+  hipError_t e = hipSuccess;
+  for (int m0 = 0; m0 < M && e == hipSuccess; m0 += 64)
+    e = run({GemmKind::kSkinny, skinny_tiles(N, Kp, epilogue), 1, 1, 0}, m0, std::min(64, M - m0));
+  return e;
 }
 
 // 2 row tiles per wave, 4 waves, K whole: 14.4 us at M=25, N=6144, K=4096

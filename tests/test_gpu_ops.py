@@ -336,3 +336,32 @@ def test_gemm_last_round_is_the_same_tiles_in_any_visiting_order(metro, M, N, K)
     differ = (outs[0] != outs[1]).nonzero()
     got = {(m, n) for m, n in torch.unique(torch.stack([differ[:, 0] // rows, differ[:, 1] // 256], 1), dim=0).tolist()}
     assert got == last
+
+
+# Rows of X so far apart that their byte offsets within one block of rows pass
+# 2^31, and 2^32: (M, N, K, epilogue, row stride).
+@pytest.mark.parametrize("M,N,K,epi,ldx", [(128, 160, 128, 0, 9_000_000), (128, 160, 128, 1, 17_000_000),
+                                           (64, 16576, 256, 0, 35_000_000), (40, 16576, 256, 2, 60_000_000),
+                                           (128, 16384, 128, 2, 17_000_000), (300, 16416, 128, 0, 8_000_000),
+                                           (300, 16416, 128, 1, 14_000_000), (300, 16416, 128, 2, 14_000_000)])
+def test_gemm_rows_far_apart(metro, M, N, K, epi, ldx):
+    print(f"far rows M={M} N={N} K={K} epi={epi} ldx={ldx}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N + epi)
+    near = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
+    X = torch.empty((M - 1) * ldx + K, dtype=torch.bfloat16, device="cuda")
+    X.as_strided((M, K), (ldx, 1)).copy_(near)
+    W = (0.05 * torch.randn(N, K, generator=g, device="cuda")).to(torch.bfloat16)
+    P = torch.empty_like(W)
+    metro.op_pack_weight(W, K, N, K, K, P)
+    for ws in (None, torch.full((8, M, N), float("nan"), device="cuda")):
+        outs = []
+        for x, ld in ((near, K), (X, ldx)):
+            out = (torch.zeros(M, N // 2, dtype=torch.bfloat16, device="cuda") if epi == 2
+                   else torch.ones(M, N, device="cuda"))
+            metro.op_gemm(x, P, M, N, K, epi, out, out.shape[1], ldx=ld, workspace=ws)
+            outs.append(out.double())
+        if epi == 2:  # fp32 sums in another order (1e-4 covers theirs) may round to the next bf16, 2^-7 of the value off
+            bound = outs[0].abs() / 128 + 1e-4
+        else:
+            bound = 1e-5 * (near.double().abs() @ W.double().abs().T) + 1e-6
+        assert bool(((outs[0] - outs[1]).abs() <= bound).all())
