@@ -59,8 +59,11 @@ metro_status metro_op_gemm(const uint16_t* X, int32_t ldx, const uint16_t* W, in
 /* The kernels metro_op_gemm would run for a product (the model chooses by the
  * same rules), for inspection and tests; host only, no device work.
  * has_workspace: nonzero as for a non-NULL workspace.  *kind: 0 decode
- * (weight streaming, or 128 x 64 blocks for large products of 33 to 64 rows), 1 tiled with 128 x 128 blocks, 2 tiled
- * with 256 (W rows) x 128 blocks, 3 tiled with 256 x 256 blocks.  *k_slices:
+ * kernel (weight streaming, up to 64 rows), 1 tiled with 128 x 128 blocks, 2
+ * tiled with 256 (W rows) x 128 blocks, 3 tiled with 256 x 256 blocks, 4 tiled
+ * with 128 x 64 blocks (33 to 64 rows).  Row strides of X that put the rows of a
+ * block more than 4 GiB apart take the decode kernel whatever the kind, 64 rows
+ * at a time and without k slices.  *k_slices:
  * k slices of every block (> 1 only with a workspace); *tail_split: k slices
  * of each block of the last, partly filled round of workgroups (1: none).
  * Counts compute units of the current device (256 when there is none).

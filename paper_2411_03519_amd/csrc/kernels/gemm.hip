@@ -315,7 +315,8 @@ using WideTile = TileShape<8, 4>;
 // 8B QKV 21.8 / 26.0 -> 16.2 / 16.7, O 15.8 / 18.7 -> 13.6 / 14.5, gate/up 47.9 /
 // 49.3 -> 43.3 / 43.6, down 30.6 / 34.3 -> 27.6 / 28.0, LM head 213 / 240 -> 195 /
 // 207; 70B QKV 51.9 / 60.4 -> 40.3 / 41.9.  At 25 and 32 rows the two are within
-// 4% (8B O 12.4 against 12.9), and the decode kernel keeps those.
+// 4% (8B O 12.4 against 12.9), and the decode kernel keeps those, as it does the
+// products that leave these tiles too few (small_tile_splits).
 using SmallTile = TileShape<4, 2>;
 
 // Grouped tile order: consecutive tiles sweep groups of GM m-tiles, m fastest
@@ -810,13 +811,6 @@ static int skinny_tiles(int N, int Kp, int epilogue) {
   return N <= 8192 && Kp <= 4096 ? 2 : 4;
 }
 
-// Whether a decode-sized product takes the Small tile: from 33 rows on, unless
-// the weights are too few (4M, i.e. 8 MB) for the activation reads to matter:
-// there both are bound by latency, and the decode kernel needs one launch.
-static bool takes_small_tile(int M, int N, int Kp) {
-  return M > kSkinnyMaxRows && static_cast<int64_t>(N) * Kp >= (1 << 22);
-}
-
 // Decode kernel: workgroups split K while fewer than `target` cover the
 // product; slices stay multiples of 128, and the slice sums (ks * M * N fp32,
 // written and read again) stay within a quarter of the weight bytes (N * Kp
@@ -855,9 +849,29 @@ static int device_cus() {
   return cache[dev];
 }
 
+// k slices with which a product of 33 to 64 rows runs as 128 x 64 tiles, 0 if
+// the decode kernel takes it.  A tile's workgroup goes through its k slice by
+// itself, where the decode kernel puts eight waves on one, so the tiles pay
+// while they occupy more than half of the CUs.  In the model, us per launch at
+// 33 / 48 / 64 rows, decode kernel against tiles: 192 workgroups (3072 x 3072)
+// 12.3 / 13.0 / 13.5 against 9.4 / 9.3 / 9.9; 128 (2048 x 2048) 6.6 / 6.7 / 7.5
+// against 7.3 / 7.4 / 7.7, (3072 x 16384, gate/up) 24.8 / 26.2 / 28.3 against
+// 32.4 / 30.8 / 31.6; 64 (11008 x 4096) 31.2 / 32.3 / 36.6 against 45.4 / 45.9 /
+// 47.0; with no workspace to hold slices, 32 (4096 x 4096) 17.7 / 18.3 / 22.0
+// against 33.2 / 33.2 / 33.7, 120 (5120 x 15360) 33.6 / 35.6 / 40.2 against 43.8 /
+// 44.5 / 46.2, 136 (4096 x 17408) 47.8 / 51.2 / 56.3 against 37.0 / 37.2 / 38.0.
+// Under 4M weights (8 MB) both are bound by latency.
+static int small_tile_splits(int M, int N, int Kp, bool split, int64_t part_cap) {
+  if (M <= kSkinnyMaxRows || static_cast<int64_t>(N) * Kp < (1 << 22)) return 0;
+  const int cus = device_cus(), tiles = (N + SmallTile::BN - 1) / SmallTile::BN;
+  int ks = split ? tiled_k_splits(tiles, cus, M, Kp) : 1;
+  while (ks > 1 && static_cast<int64_t>(ks) * M * N > part_cap) ks /= 2;
+  return 2 * tiles * ks > cus ? ks : 0;
+}
+
 // Kernel choice, from probes over M = 80 .. 12800 at the Llama-3-8B and 70B
 // shapes: decode batches (up to 64 rows) the decode kernel or the Small tile
-// (takes_small_tile); then 128 x 128 tiles (more blocks)
+// (small_tile_splits); then 128 x 128 tiles (more blocks)
 // for narrow products, and for wide ones up to 192 rows while their tiles
 // number at most the CUs (in the 70B model at M=128 gate/up took 242 us as 448
 // such tiles against 203 us as 224 of 256 x 256, although cache-cold probes
@@ -870,12 +884,14 @@ GemmPlan plan_gemm(int M, int N, int Kp, int epilogue, int64_t part_cap) {
   const bool can_split = part_cap > 0;
   const bool split = can_split && epilogue != kEpiSwiGLU && M <= kSplitMaxRows;
   if (M <= 64) {
-    p.kind = GemmKind::kSkinny;
-    p.nt = takes_small_tile(M, N, Kp) ? 0 : skinny_tiles(N, Kp, epilogue);
-    if (split && p.nt == 0)
-      p.ks = tiled_k_splits((N + SmallTile::BN - 1) / SmallTile::BN, device_cus(), M, Kp);
-    else if (split)
-      p.ks = gemm_k_splits(N / (16 * p.nt), p.nt == 2 ? 512 : 256, M, Kp);
+    if (const int ks = small_tile_splits(M, N, Kp, split, part_cap)) {
+      p.kind = GemmKind::kSmall;
+      p.ks = ks;
+    } else {
+      p.kind = GemmKind::kSkinny;
+      p.nt = skinny_tiles(N, Kp, epilogue);
+      if (split) p.ks = gemm_k_splits(N / (16 * p.nt), p.nt == 2 ? 512 : 256, M, Kp);
+    }
     while (p.ks > 1 && static_cast<int64_t>(p.ks) * M * N > part_cap) p.ks /= 2;
     return p;
   }
@@ -989,14 +1005,15 @@ static hipError_t launch_epi(const GemmPlan& p, const uint16_t* X, int ldx, cons
                              float* outf, uint16_t* outb, int ldo, float* part, hipStream_t s) {
   switch (p.kind) {
     case GemmKind::kSkinny:
-      if (p.nt == 0)
-        launch_tiled<SmallTile, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
-      else if (p.nt == 7)
+      if (p.nt == 7)
         launch_skinny_m<7, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
       else if (p.nt == 4)
         launch_skinny_m<4, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
       else
         launch_skinny_m<2, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
+      break;
+    case GemmKind::kSmall:
+      launch_tiled<SmallTile, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
       break;
     case GemmKind::kMid:
       even_rows(M, MidTile::BM, [&](auto tm) {
@@ -1025,10 +1042,10 @@ static hipError_t launch_epi(const GemmPlan& p, const uint16_t* X, int ldx, cons
 // The tiled kernel reaches the rows of a block by 32-bit byte offsets from the
 // block's first element (they are 32 bits wide in the load itself).
 static bool offsets_fit(const GemmPlan& p, int M, int ldx, int Kp) {
-  if (p.kind == GemmKind::kSkinny && p.nt != 0) return true;  // 64-bit pointers
-  const bool big = p.kind == GemmKind::kBig, wide = p.kind == GemmKind::kWide, small = p.kind == GemmKind::kSkinny;
-  const int bn = big || wide ? BigTile::BN : MidTile::BN;
-  const int bm = big ? BigTile::BM : small ? SmallTile::BM : MidTile::BM;
+  if (p.kind == GemmKind::kSkinny) return true;  // 64-bit pointers
+  const bool big = p.kind == GemmKind::kBig;
+  const int bn = big || p.kind == GemmKind::kWide ? BigTile::BN : MidTile::BN;
+  const int bm = big ? BigTile::BM : p.kind == GemmKind::kSmall ? SmallTile::BM : MidTile::BM;
   constexpr int64_t kMax = int64_t{1} << 32;
   return 2ll * ldx * std::min(M, bm) <= kMax && 2ll * Kp * bn <= kMax;
 }
@@ -1064,17 +1081,25 @@ hipError_t launch_gemm(const uint16_t* X, int ldx, const uint16_t* W, int Kp, in
   return e;
 }
 
-// 2 row tiles per wave, 4 waves, K whole: 14.4 us at M=25, N=6144, K=4096
-// (with 4 k slices the product alone takes 13.1 us, but the slice sums then
-// cost a RoPE kernel of 5.2 us)
-bool gemm_rope_kv_fused(int M, int N, int Kp) {
-  return (M <= kRopeKVMaxRows && !takes_small_tile(M, N, Kp)) || plan_gemm(M, N, Kp, kEpiStoreF32, 0).kind == GemmKind::kBig;
+// Decode kernel: 2 row tiles per wave, 4 waves, K whole: 14.4 us at M=25,
+// N=6144, K=4096 (with 4 k slices the product alone takes 13.1 us, but the slice
+// sums then cost a RoPE kernel of 5.2 us).  128 x 64 tiles and the RoPE kernel
+// cost less once K is kOwnSumMinK or more.  In the model, us per layer at 33 / 48
+// / 64 rows, fused against product + RoPE: K 2048, N 6144 13.2 / 13.4 / 15.4
+// against 14.2 / 14.5 / 15.2; 2560, 7680 17.9 / 18.1 / 19.5 against 17.7 / 19.2 /
+// 19.0; 3072, 9216 27.8 / 29.7 / 34.8 against 25.0 / 25.1 / 25.2; 4096, 6144
+// 23.6 / 22.9 / 24.4 against 21.2 / 20.9 / 21.9.
+bool gemm_rope_kv_fused(int M, int N, int Kp, int64_t part_cap) {
+  if (M <= kRopeKVMaxRows)
+    return Kp < kOwnSumMinK || plan_gemm(M, N, Kp, kEpiStoreF32, part_cap).kind != GemmKind::kSmall;
+  return plan_gemm(M, N, Kp, kEpiStoreF32, 0).kind == GemmKind::kBig;
 }
 
 hipError_t launch_gemm_rope_kv(const uint16_t* X, int ldx, const uint16_t* W, int Kp, int M, int N, const RopeKV& rk,
                                hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  if (!gemm_rope_kv_fused(M, N, Kp) || N != (rk.nq + 2 * rk.nkv) * rk.hd || rk.hd % 32 || N % 32)
+  if ((M > kRopeKVMaxRows && !gemm_rope_kv_fused(M, N, Kp, 0)) || N != (rk.nq + 2 * rk.nkv) * rk.hd || rk.hd % 32 ||
+      N % 32)
     return hipErrorInvalidValue;
   if (M > kRopeKVMaxRows) {  // 256 x 256 tiles over all of K (no workspace: no split of the last round)
     even_rows(M, BigTile::BM, [&](auto tm) {

@@ -138,20 +138,24 @@ struct RopeKV {
 // one with 256-row tiles (any epilogue) may split only the tiles of its last,
 // partly filled round (up to CUs * 256 * 256 floats of part), and completes
 // them itself (*n_parts stays 0).
-// Kernel choice (plan_gemm): up to 64 rows the decode kind (weight streaming, or
-// 128 x 64 tiles for large products of 33 rows and more); then the tiled GEMM with 128 x 128 blocks (narrow products up to
-// kMidMaxRows rows, wide ones while they fit the CUs), 256 (W rows) x 128
-// blocks (wide products at up to 256 rows otherwise, narrow ones of up to 128
-// rows that 128 x 128 blocks would leave mostly idle), or 256 x 256 blocks.
-enum class GemmKind { kSkinny, kMid, kWide, kBig };
+// Kernel choice (plan_gemm): up to 64 rows the decode kernel (weight streaming)
+// or, for large products of 33 rows and more, the tiled GEMM with 128 (W rows)
+// x 64 blocks; then with 128 x 128 blocks (narrow products up to kMidMaxRows
+// rows, wide ones while they fit the CUs), 256 (W rows) x 128 blocks (wide
+// products at up to 256 rows otherwise, narrow ones of up to 128 rows that 128 x
+// 128 blocks would leave mostly idle), or 256 x 256 blocks.
+enum class GemmKind { kSkinny, kMid, kWide, kBig, kSmall };
 struct GemmPlan {
   GemmKind kind;
-  int nt;          // row tiles per wave (decode kernel; 0: 128 x 64 tiles)
+  int nt;          // row tiles per wave (decode kernel)
   int ks;          // k slices of every tile
   int tail_split;  // k slices of each tile from tail_first on (1: none)
   int tail_first;
 };
 constexpr int kSkinnyMaxRows = 32;  // rows up to which every product streams its weights
+// k from which slices of a product of 33 to 64 rows save more than the launch
+// that then adds them (the RoPE kernel behind QKV, the sum behind the LM head)
+constexpr int kOwnSumMinK = 3072;
 constexpr int kMidMaxRows = 1000;
 constexpr int kSplitMaxRows = 1024;
 GemmPlan plan_gemm(int M, int N, int Kp, int epilogue, int64_t part_cap);
@@ -159,14 +163,14 @@ hipError_t launch_gemm(const uint16_t* X, int ldx, const uint16_t* W, int Kp, in
                        float* out_f32, uint16_t* out_bf16, int ldo, float* part, int64_t part_cap, int* n_parts,
                        hipStream_t s);
 // QKV projection (N = (nq + 2 nkv) * hd) with RoPE and the KV cache write in
-// its epilogue, in place of launch_gemm + launch_rope_kv, for the shapes
-// gemm_rope_kv_fused accepts: up to kRopeKVMaxRows rows (decode kernel; not
-// where 128 x 64 tiles with k slices and the RoPE kernel cost less: 8B at M = 64
-// 26 against 16.7 + 5.4 us), or
-// the batches plan_gemm gives 256 x 256 tiles (prefill chunks); K is not split,
-// so no slice sums are left.  hipErrorInvalidValue for other shapes.
+// its epilogue, in place of launch_gemm + launch_rope_kv.  gemm_rope_kv_fused:
+// where that is what to launch, given part_cap floats for slice sums otherwise:
+// up to kRopeKVMaxRows rows (decode kernel; any shape may), unless 128 x 64
+// tiles and the RoPE kernel cost less, and the batches plan_gemm gives 256 x 256
+// tiles (prefill chunks).  K is not split, so no slice sums are left.
+// hipErrorInvalidValue for other shapes.
 constexpr int kRopeKVMaxRows = 64;
-bool gemm_rope_kv_fused(int M, int N, int Kp);
+bool gemm_rope_kv_fused(int M, int N, int Kp, int64_t part_cap);
 hipError_t launch_gemm_rope_kv(const uint16_t* X, int ldx, const uint16_t* W, int Kp, int M, int N, const RopeKV& rk,
                                hipStream_t s);
 // Apply the fp32 epilogue to KS slices: out (=|+=) sum_s part[s].

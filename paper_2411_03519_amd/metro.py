@@ -292,7 +292,7 @@ def op_gemm(X, W, M: int, N: int, Kp: int, epilogue: int, out, ldo: int, ldx: in
                             _ptr(b16), ldo, _ptr(workspace), _stream(stream)))
 
 
-GEMM_KINDS = ("decode", "tile128x128", "tile256x128", "tile256x256")
+GEMM_KINDS = ("decode", "tile128x128", "tile256x128", "tile256x256", "tile128x64")
 
 
 def op_gemm_plan(M: int, N: int, Kp: int, epilogue: int, workspace: bool = False):

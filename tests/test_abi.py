@@ -55,6 +55,17 @@ PLAN_CASES = [
     (25, 6144, 4096, 0, True, "decode", 2, 1),          # decode QKV: too few blocks, K split
     (25, 28672, 4096, 2, True, "decode", 1, 1),         # SwiGLU never splits K
     (64, 4096, 14336, 1, False, "decode", 1, 1),        # no workspace, no split
+    (32, 4096, 4096, 1, True, "decode", 2, 1),          # up to 32 rows every product streams its weights
+    (33, 4096, 4096, 1, True, "tile128x64", 8, 1),      # 32 tiles x 8 slices
+    (64, 28672, 4096, 2, False, "tile128x64", 1, 1),    # 8B gate/up: 224 tiles
+    (48, 128256, 4096, 0, False, "tile128x64", 1, 1),   # 8B LM head
+    (48, 1024, 2048, 1, True, "decode", 2, 1),          # under 4M weights: the decode kernel
+    (33, 4096, 4096, 1, False, "decode", 1, 1),         # no slices: 32 tiles would leave 7 of 8 CUs idle
+    (64, 4096, 11008, 1, True, "decode", 2, 1),         # K of few factors: 32 tiles x 2 slices
+    (64, 16384, 4096, 2, True, "decode", 1, 1),         # 128 tiles: half of the CUs
+    (64, 17408, 4096, 2, True, "tile128x64", 1, 1),     # 136 tiles
+    (64, 2048, 2048, 1, True, "decode", 4, 1),          # 16 tiles x 8 slices
+    (64, 3072, 3072, 1, True, "tile128x64", 8, 1),      # 24 tiles x 8 slices
     (65, 4096, 4096, 1, False, "tile128x128", 1, 1),    # past 64 rows: tiled
     (1000, 6144, 4096, 0, False, "tile128x128", 1, 1),  # narrow up to 1000 rows
     (1001, 6144, 4096, 0, False, "tile256x256", 1, 1),
