@@ -1095,6 +1095,8 @@ bool gemm_rope_kv_fused(int M, int N, int Kp, int64_t part_cap) {
   return plan_gemm(M, N, Kp, kEpiStoreF32, 0).kind == GemmKind::kBig;
 }
 
+bool gemm_slices_pay_a_sum(int M, int Kp) { return M > 64 || (M > kSkinnyMaxRows && Kp >= kOwnSumMinK); }
+
 hipError_t launch_gemm_rope_kv(const uint16_t* X, int ldx, const uint16_t* W, int Kp, int M, int N, const RopeKV& rk,
                                hipStream_t s) {
   if (M <= 0) return hipSuccess;

@@ -156,6 +156,14 @@ constexpr int kSkinnyMaxRows = 32;  // rows up to which every product streams it
 // k from which slices of a product of 33 to 64 rows save more than the launch
 // that then adds them (the RoPE kernel behind QKV, the sum behind the LM head)
 constexpr int kOwnSumMinK = 3072;
+// Whether k slices are worth giving a product whose sum takes a launch of its
+// own (the LM head's).  At 33 / 48 / 64 rows and 4096 columns, whole against
+// slices and sum, in the model: K 1024 6.8 / 7.3 / 8.5 against 10.8 / 10.9 / 11.3
+// us, 2048 11.0 / 11.9 / 13.8 against 12.3 / 12.5 / 13.0, 2560 12.7 / 13.7 / 16.2
+// against 15.4 / 15.6 / 15.9, 3072 14.7 / 15.5 / 18.3 against 13.9 / 14.5 / 14.8,
+// 4096 18.8 / 19.3 / 22.8 against 15.3 / 15.5 / 15.8; above 64 rows the tiled
+// kernels go through K alone (4096 x 8192 at 128 rows 71 us as 32 blocks).
+bool gemm_slices_pay_a_sum(int M, int Kp);
 constexpr int kMidMaxRows = 1000;
 constexpr int kSplitMaxRows = 1024;
 GemmPlan plan_gemm(int M, int N, int Kp, int epilogue, int64_t part_cap);

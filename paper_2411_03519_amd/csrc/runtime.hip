@@ -328,11 +328,10 @@ metro_status launch_head(metro_model* m, float* xrows, int R, int x_parts, float
                                x_parts, s));
   LAUNCH(m, METRO_K_LM_HEAD, s,
          metro::launch_gemm(m->h, c.d_model, m->lm_head, c.d_model, R, c.vocab, metro::kEpiStoreF32, lg, nullptr,
-                            c.vocab, R > metro::kSkinnyMaxRows ? m->parts : nullptr, m->parts_cap, &lp, s));
-  // (a small vocabulary leaves most CUs idle without k slices: 4096 x 8192 at
-  // 128 rows 71 us as 32 blocks; the decode kernel spreads over them as it is,
-  // and slices would cost it the sum's launch.  The norm above has taken the
-  // pending slices.)
+                            c.vocab, metro::gemm_slices_pay_a_sum(R, c.d_model) ? m->parts : nullptr, m->parts_cap,
+                            &lp, s));
+  // (a small vocabulary leaves most CUs idle without k slices; the norm above
+  // has taken the pending slices)
   if (lp > 0)
     LAUNCH(m, METRO_K_LM_HEAD, s,
            metro::launch_reduce_parts(m->parts, lp, R, c.vocab, metro::kEpiStoreF32, lg, c.vocab, s));

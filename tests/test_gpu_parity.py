@@ -217,6 +217,34 @@ def test_one_token_items_match_decode_steps(metro, only_single):
         assert (got[keep] - want).abs().max().item() <= 2e-2
 
 
+@pytest.mark.parametrize("d,vocab,launches", [(1024, 1024, 1), (1024, 4096, 1), (2048, 4096, 1), (4096, 1024, 2),
+                                              (4096, 4096, 2)])
+def test_head_of_a_small_vocabulary(metro, d, vocab, launches):
+    """At 33 to 64 rows the LM head has k slices, and a launch that adds them,
+    only where d_model is long enough; the logits are those of smaller batches
+    up to the fp32 rounding of other sum orders (rel-L2 5e-3 of the row, as
+    measured across batch sizes at these widths)."""
+    shape = dict(synth.TINY, n_layers=1, d_model=d, n_heads=d // 128, n_kv_heads=d // 512, head_dim=128, vocab=vocab)
+    with metro.Model(shape, max_batch=64, max_tokens=64, max_context=64, kv_pool_bytes=64 << 20) as m:
+        for B in (33, 64):
+            toks = np.arange(B, dtype=np.int32) * 7 % vocab
+            got, want = (torch.empty(B, vocab, device="cuda") for _ in range(2))
+            seqs = [m.seq_open() for _ in range(B)]
+            m.profile_start("lm_head", "decode")
+            m.decode_step(seqs, toks, got)
+            assert m.profile_stop()[1] == launches
+            for s in seqs:
+                m.seq_close(s)
+            for r0 in range(0, B, 32):
+                n = min(32, B - r0)
+                seqs = [m.seq_open() for _ in range(n)]
+                m.decode_step(seqs, toks[r0:r0 + n], want[r0:r0 + n])
+                for s in seqs:
+                    m.seq_close(s)
+            torch.cuda.synchronize()
+            assert bool(((got - want).norm(dim=1) <= 5e-3 * want.norm(dim=1)).all())
+
+
 def test_decode_rows_independent_of_batch_composition(metro):
     w = synth.llama_weights(synth.TINY, 1)
     rng = np.random.default_rng(21)
