@@ -983,21 +983,22 @@ static void launch_tiled(const uint16_t* X, int ldx, const uint16_t* W, int Kp, 
   }
 }
 
+// go with the smallest of LO .. HI that is at least tm (HI if none is)
+template <int LO, int HI, class Go>
+static void at_least(int tm, Go&& go) {
+  if constexpr (LO < HI) {
+    if (tm > LO) return at_least<LO + 1, HI>(tm, go);
+  }
+  go(std::integral_constant<int, LO>{});
+}
+
 // Row blocks of 32 TM rows: as many as the kind's full blocks would be, evened
 // out, so that no block works on many absent rows (M = 301: 2 x 160 instead of
-// 2 x 256).
-template <class Go>
-static void even_rows(int M, int bm, Go&& go) {
-  const int blocks = (M + bm - 1) / bm, tm = ((M + blocks - 1) / blocks + 31) / 32;
-  if (bm == BigTile::BM) {
-    if (tm <= 5) go(std::integral_constant<int, 5>{});
-    else if (tm == 6) go(std::integral_constant<int, 6>{});
-    else if (tm == 7) go(std::integral_constant<int, 7>{});
-    else go(std::integral_constant<int, 8>{});
-  } else {
-    if (tm <= 3) go(std::integral_constant<int, 3>{});
-    else go(std::integral_constant<int, 4>{});
-  }
+// 2 x 256).  LO: the least TM built.
+template <class S, int LO, class Go>
+static void even_rows(int M, Go&& go) {
+  const int blocks = (M + S::BM - 1) / S::BM;
+  at_least<LO, S::TM>(((M + blocks - 1) / blocks + 31) / 32, go);
 }
 
 template <int EPI>
@@ -1016,23 +1017,20 @@ static hipError_t launch_epi(const GemmPlan& p, const uint16_t* X, int ldx, cons
       launch_tiled<SmallTile, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
       break;
     case GemmKind::kMid:
-      even_rows(M, MidTile::BM, [&](auto tm) {
-        if constexpr (tm <= 4)
-          launch_tiled<TileShape<MidTile::TN, tm>, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
+      even_rows<MidTile, 3>(M, [&](auto tm) {
+        launch_tiled<TileShape<MidTile::TN, tm>, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s);
       });
       break;
     case GemmKind::kWide:
-      even_rows(M, WideTile::BM, [&](auto tm) {
-        if constexpr (tm <= 4)
-          launch_tiled<TileShape<WideTile::TN, tm>, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s,
-                                                         p.tail_split, p.tail_first);
+      even_rows<WideTile, 3>(M, [&](auto tm) {
+        launch_tiled<TileShape<WideTile::TN, tm>, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s,
+                                                       p.tail_split, p.tail_first);
       });
       break;
     case GemmKind::kBig:
-      even_rows(M, BigTile::BM, [&](auto tm) {
-        if constexpr (tm > 4)
-          launch_tiled<TileShape<BigTile::TN, tm>, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s,
-                                                        p.tail_split, p.tail_first);
+      even_rows<BigTile, 5>(M, [&](auto tm) {
+        launch_tiled<TileShape<BigTile::TN, tm>, EPI>(X, ldx, W, Kp, M, N, outf, outb, ldo, part, p.ks, s,
+                                                      p.tail_split, p.tail_first);
       });
       break;
   }
@@ -1104,13 +1102,11 @@ hipError_t launch_gemm_rope_kv(const uint16_t* X, int ldx, const uint16_t* W, in
       N % 32)
     return hipErrorInvalidValue;
   if (M > kRopeKVMaxRows) {  // 256 x 256 tiles over all of K (no workspace: no split of the last round)
-    even_rows(M, BigTile::BM, [&](auto tm) {
-      if constexpr (tm > 4) {
-        using S = TileShape<BigTile::TN, tm>;
-        const int tiles = ((N + S::BN - 1) / S::BN) * ((M + S::BM - 1) / S::BM);
-        launch_kernel((gemm_tiled_kernel<S, kEpiRopeKV>), dim3(tiles, 1), dim3(S::NTH), 0, s, X, ldx, W, Kp, M, N,
-                      nullptr, nullptr, 0, nullptr, 0, 1, rk);
-      }
+    even_rows<BigTile, 5>(M, [&](auto tm) {
+      using S = TileShape<BigTile::TN, tm>;
+      const int tiles = ((N + S::BN - 1) / S::BN) * ((M + S::BM - 1) / S::BM);
+      launch_kernel((gemm_tiled_kernel<S, kEpiRopeKV>), dim3(tiles, 1), dim3(S::NTH), 0, s, X, ldx, W, Kp, M, N,
+                    nullptr, nullptr, 0, nullptr, 0, 1, rk);
     });
     return hipGetLastError();
   }
