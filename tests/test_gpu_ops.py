@@ -1,8 +1,8 @@
 """Single kernels of the HIP path against CPU references (through metro_ops.h).
 
 Weight packing: bit-exact against the operand-order layout written out.
-GEMM: every epilogue, in the skinny (M <= 64) and tiled (M > 64) kernels,
-with ragged M, K padded to 128 and N covering several tiles plus a tail.
+GEMM: every epilogue, in the decode kernel (M <= 64) and the tiled kernel (M >
+32), with ragged M, K padded to 128 and N covering several tiles plus a tail.
 The reference products are exact-value float64 sums of the same bf16
 operands; the GPU accumulates in fp32, so the bound is a few fp32 ulps of
 the row's absolute sum.
@@ -73,7 +73,8 @@ def test_pack_weight_rejects_bad_shapes(metro):
             metro.op_pack_weight(W, ld, N, K, Kp, out)
 
 
-# (M, K, N): decode kernel at M <= 64; above it the tiled kernel with 128 x 128
+# (M, K, N): decode kernel at M <= 64 (the 128 x 64 blocks that large products of
+# 33 rows and more take are below); above it the tiled kernel with 128 x 128
 # blocks (narrow products up to 1000 rows, wide ones up to 192 while they fit
 # the CUs), 256 x 128 blocks (wide products otherwise, up to 256 rows) or 256 x
 # 256 blocks, with or without a k split (plan_gemm); the 256-row tiles split
@@ -216,12 +217,15 @@ def test_argmax_short_and_ragged_rows(metro, V):
     np.testing.assert_array_equal(out.cpu().numpy(), want)
 
 
-# One shape per kernel kind and epilogue: decode kernel with 1, 2 and 4
-# activation tiles and 2, 4 and 7 row tiles per wave, 128 x 128, 256 x 128 and
-# 256 x 256 tiles, k slices, a split last round, SwiGLU.
-REPEAT_CASES = [(7, 4096, 6144, 0, True), (25, 4096, 4096, 1, True), (25, 4096, 28672, 2, False),
-                (60, 14336, 4096, 1, True), (128, 4096, 4096, 1, True), (128, 4096, 28672, 2, False),
-                (200, 4096, 10240, 0, True), (1300, 2048, 4096, 1, True), (2600, 4096, 6144, 0, False)]
+# (M, K, N, epilogue, workspace) and the kernel that runs: decode kernel with 1, 2
+# and 4 activation tiles and 2, 4 and 7 row tiles per wave, 128 x 64, 128 x 128,
+# 256 x 128 and 256 x 256 tiles, k slices, a split last round, SwiGLU.
+REPEAT_CASES = [(7, 4096, 6144, 0, True, "decode"), (25, 4096, 4096, 1, True, "decode"),
+                (25, 4096, 28672, 2, False, "decode"), (48, 2048, 1024, 1, True, "decode"),
+                (60, 11008, 4096, 1, True, "decode"), (60, 14336, 4096, 1, True, "tile128x64"),
+                (128, 4096, 4096, 1, True, "tile128x128"), (128, 4096, 28672, 2, False, "tile128x128"),
+                (200, 4096, 10240, 0, True, "tile128x128"), (128, 4096, 10240, 0, True, "tile256x128"),
+                (1300, 2048, 4096, 1, True, "tile256x256"), (2600, 4096, 6144, 0, False, "tile256x256")]
 
 
 def test_gemm_repeated_launches_are_bitwise_stable(metro):
@@ -231,7 +235,9 @@ def test_gemm_repeated_launches_are_bitwise_stable(metro):
     launch), and its first result is within the fp32 bound of the exact one."""
     rng = np.random.default_rng(77)
     cases = []
-    for M, K, N, epi, split in REPEAT_CASES:
+    for M, K, N, epi, split, kind in REPEAT_CASES:
+        plan = metro.op_gemm_plan(M, N, K, epi, split)
+        assert plan[0] == kind
         X = rand_bf16(rng, (M, K))
         W = rand_bf16(rng, (N, K), 0.05)
         swig = epi == 2
@@ -262,21 +268,9 @@ def test_gemm_repeated_launches_are_bitwise_stable(metro):
                 np.testing.assert_array_equal(got, first[i], err_msg=f"case {c[:5]} launch {rep}")
 
 
-# Row blocks of the tiled kernel: 64 rows from 33 to 64 rows on for products of
-# 4M weights and more; above, evened out over the rows (32 TM rows, TM 3 or 4 for
-# 128-row blocks, 5 .. 8 for 256-row ones).  Both sides of each step, with a last
-# block that is nearly empty, ragged N, and k slices / a split last round when
-# given a workspace.
-EVEN_ROWS = [(32, 16384), (33, 16384), (48, 11008), (64, 28672), (64, 1056), (96, 1056), (97, 1056), (192, 160), (193, 16384), (192, 28672),
-             (257, 16416), (320, 16384), (321, 16384),
-             (385, 16384), (449, 16384), (513, 16384), (1001, 288), (1025, 288), (1281, 160)]
-
-
-@pytest.mark.parametrize("M,N", EVEN_ROWS)
-@pytest.mark.parametrize("epi", [0, 1, 2])
-def test_gemm_even_row_blocks(metro, M, N, epi):
-    print(f"even rows M={M} N={N} epi={epi}", flush=True)
-    K = 384
+def check_product(metro, M, N, K, epi, workspaces):
+    """op_gemm with each workspace against the float64 product, within a few
+    fp32 ulps of the rows' absolute sums (and one bf16 ulp after SwiGLU)."""
     g = torch.Generator(device="cuda").manual_seed(M + N + epi)
     X = torch.randn(M, K, generator=g, device="cuda").to(torch.bfloat16)
     W = (0.05 * torch.randn(N, K, generator=g, device="cuda")).to(torch.bfloat16)
@@ -284,8 +278,8 @@ def test_gemm_even_row_blocks(metro, M, N, epi):
     metro.op_pack_weight(W, K, N, K, K, P)
     ref = X.double() @ W.double().T
     err = 1e-5 * (X.double().abs() @ W.double().abs().T) + 1e-6
-    outs = []
-    for ws in (None, torch.full((8, M, N), float("nan"), device="cuda")):
+    for ws in workspaces:
+        ws = torch.full((8, M, N), float("nan"), device="cuda") if ws else None
         if epi == 2:
             out = torch.zeros(M, N // 2, dtype=torch.bfloat16, device="cuda")
             metro.op_gemm(X, P, M, N, K, epi, out, N // 2, workspace=ws)
@@ -300,6 +294,50 @@ def test_gemm_even_row_blocks(metro, M, N, epi):
             metro.op_gemm(X, P, M, N, K, epi, out, N, workspace=ws)
             want, bound = ref + (init.double() if epi == 1 else 0.0), err
         assert bool(((out.double() - want).abs() <= bound).all())
+
+
+# Row blocks of the tiled kernel: 64 rows for 33 to 64 rows, where the tiles are
+# enough; above, evened out over the rows (32 TM rows, TM 3 or 4 for 128-row
+# blocks, 5 .. 8 for 256-row ones).  Both sides of each step, with a last block
+# that is nearly empty and ragged N.  K = 384 is too short for k slices.
+EVEN_ROWS = [(32, 16384), (33, 16384), (33, 17408), (48, 11008), (48, 16672), (64, 28672), (64, 1056), (96, 1056),
+             (97, 1056), (192, 160), (193, 16384), (192, 28672), (257, 16416), (320, 16384), (321, 16384),
+             (385, 16384), (449, 16384), (513, 16384), (1001, 288), (1025, 288), (1281, 160)]
+
+
+@pytest.mark.parametrize("M,N", EVEN_ROWS)
+@pytest.mark.parametrize("epi", [0, 1, 2])
+def test_gemm_even_row_blocks(metro, M, N, epi):
+    print(f"even rows M={M} N={N} epi={epi}", flush=True)
+    check_product(metro, M, N, 384, epi, (False, True))
+
+
+# The same blocks with k slices, or a last round cut into them: M, N, K,
+# epilogue -> kind, k slices, k slices of the last round.
+SPLIT_BLOCKS = [(33, 4000, 2048, 0, "tile128x64", 8, 1),      # 64 rows, ragged in M and N
+                (48, 3104, 3072, 1, "tile128x64", 8, 1),
+                (64, 6176, 4096, 0, "tile128x64", 4, 1),
+                (80, 4000, 1024, 1, "tile128x128", 2, 1),     # 96 rows
+                (192, 4000, 4096, 0, "tile128x128", 4, 1),    # 2 x 96
+                (128, 1056, 2048, 1, "tile128x128", 4, 1),    # 128
+                (80, 10240, 4096, 0, "tile256x128", 4, 1),    # 96
+                (128, 10208, 4096, 1, "tile256x128", 4, 1),   # 128
+                (80, 69632, 1024, 0, "tile256x128", 1, 8),    # 96, last round
+                (80, 69632, 1024, 2, "tile256x128", 1, 8),
+                (300, 16384, 4096, 0, "tile256x256", 2, 1),   # 2 x 160
+                (300, 16384, 1024, 2, "tile256x256", 1, 2),
+                (384, 16384, 4096, 1, "tile256x256", 2, 1),   # 2 x 192
+                (576, 28672, 512, 2, "tile256x256", 1, 2),    # 3 x 192 (8B gate/up)
+                (440, 16384, 4096, 0, "tile256x256", 2, 1),   # 2 x 224
+                (660, 28672, 512, 2, "tile256x256", 1, 2),    # 3 x 224
+                (660, 28640, 512, 1, "tile256x256", 1, 2)]
+
+
+@pytest.mark.parametrize("M,N,K,epi,kind,ks,tail", SPLIT_BLOCKS)
+def test_gemm_split_row_blocks(metro, M, N, K, epi, kind, ks, tail):
+    print(f"split blocks M={M} N={N} K={K} epi={epi}", flush=True)
+    assert metro.op_gemm_plan(M, N, K, epi, True) == (kind, ks, tail)
+    check_product(metro, M, N, K, epi, (True,))
 
 
 @pytest.mark.parametrize("M,N,K", [(1500, 12288, 1024),    # 6 x 48 tiles of 256 x 256: the last 32
