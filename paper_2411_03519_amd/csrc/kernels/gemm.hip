@@ -58,7 +58,7 @@ __device__ __forceinline__ void store_swiglu(f32x4 gt, f32x4 up, int m, int j, u
 // slice (grid.y = KS slices); wave w takes the 128-wide k blocks w, w+NW, ...
 // of the slice.  A block is 4 packed 16 x 32 tiles per row tile, i.e. 4 KiB
 // contiguous in W, read as four 1 KiB wave loads.
-// Partial tiles of the 8 waves are summed through LDS in wave order; with
+// Partial tiles of the NW waves are summed through LDS in wave order; with
 // KS > 1 the slice sums go to part[slice][m][n] and the consumer kernel adds
 // the slices (in slice order) where it reads the result.
 // ---------------------------------------------------------------------------
@@ -305,7 +305,7 @@ struct TileShape {
 // 8-wave kernels of these tile sizes (32x32x16 MFMAs): 8B gate/up at M = 128 /
 // 200 / 256 50.8 / 75.2 / 83.1 -> 49.6 / 63.8 / 68.0 us, down at M = 200 45.3 ->
 // 42.2, O at M = 800 41.1 -> 36.6; 70B gate/up at M = 128 194 -> 172, QKV 56.5
-// -> 47.3; within 2% either way for the 70B down and QKV at M = 160..301.
+// -> 47.3; 70B down and QKV at M = 129 .. 384 from 2% slower to 9% faster.
 using BigTile = TileShape<8, 8>;
 using MidTile = TileShape<4, 4>;
 using WideTile = TileShape<8, 4>;
@@ -374,7 +374,7 @@ __device__ __forceinline__ void full_tile_origin(int t, int full, int M, int N, 
 // every XCD gets a contiguous run of the work list: in tile_origin order the
 // row tiles that read the same W columns are neighbours, so they run on one
 // XCD and share its L2 instead of each fetching W through the fabric.  In the
-// model (agent trace, 8B) this gained 2.5%.
+// model (agent trace, 8B, with 8-wave 128 x 128 tiles) this gained 2.5%.
 __device__ __forceinline__ int xcd_contiguous(int b, int total) {
   constexpr int kXcds = 8;
   const int q = total / kXcds, r = total % kXcds, x = b % kXcds, s = b / kXcds;
@@ -823,13 +823,13 @@ static int gemm_k_splits(int blocks, int target, int M, int Kp) {
 
 // Tiled kernels: the most k slices (a power of two up to 8, slices multiples
 // of 128) whose workgroups still fit one round of the CUs, with slice sums up
-// to half the weight bytes (4 * ks * M <= Kp).  At M = 80..256 the narrow
-// 8B/70B products ran fastest with one round of workgroups (8B O at M=200: 4
-// slices, 256 workgroups, 26 us; 2 slices 30 us; 8B down at M=200: 4 slices
-// 50 us, 8 slices over 512 workgroups 57 us); in the model this took the
-// agent trace from 11.7k to 12.2k tokens/s and the 70B step (B=128) from
-// 2.47k to 2.57k against the former rule (fewer than 512 workgroups for
-// 128 x 128 tiles, slice sums within a quarter of the weights).
+// to half the weight bytes (4 * ks * M <= Kp).  Cache-cold, sum included, us for
+// 1 / 2 / 4 / 8 slices of 128 x 128 tiles: 8B O at M = 80 35.4 / 23.1 / 18.0 /
+// 16.0, at M = 200 36.2 / 24.6 / 20.3 / 23.7, at M = 301 35.8 / 25.9 / 28.6 / 31.7
+// (the rule: 8, 4, 2); 8B down at M = 200 113.8 / 65.0 / 42.5 / 45.6 (4); 70B down
+// at M = 128 257 / 149 / 105 (4).  Two workgroups of these tiles fit a CU, and
+// with a long K a second round's worth of slices can pay: 8B down at M = 301 2
+// slices 65.7, 8 62.1; 70B down at M = 200 2 slices 155.9, 4 143.3.
 static int tiled_k_splits(int tiles, int cus, int M, int Kp) {
   int ks = 1;
   while (ks < 8 && tiles * (2 * ks) <= cus && (Kp / (2 * ks)) % 128 == 0 && 4 * (2 * ks) * M <= Kp) ks *= 2;
@@ -869,16 +869,24 @@ static int small_tile_splits(int M, int N, int Kp, bool split, int64_t part_cap)
   return 2 * tiles * ks > cus ? ks : 0;
 }
 
-// Kernel choice, from probes over M = 80 .. 12800 at the Llama-3-8B and 70B
-// shapes: decode batches (up to 64 rows) the decode kernel or the Small tile
-// (small_tile_splits); then 128 x 128 tiles (more blocks)
-// for narrow products, and for wide ones up to 192 rows while their tiles
-// number at most the CUs (in the 70B model at M=128 gate/up took 242 us as 448
-// such tiles against 203 us as 224 of 256 x 256, although cache-cold probes
-// had ranked them the other way); else 256 x 128 tiles for wide products up to
-// 128 rows, or up to 256 while they number at most the CUs, and for narrow
-// products of up to 128 rows that 128 x 128 tiles leave mostly idle; 256 x 256
-// tiles for the rest and for long prefill chunks.
+// Kernel choice: decode batches (up to 64 rows) the decode kernel or the Small
+// tile (small_tile_splits); then 128 x 128 tiles (more blocks) for narrow
+// products, and for wide ones up to 192 rows while their tiles number at most
+// the CUs; else 256 x 128 tiles for wide products up to 128 rows, or up to 256
+// while they number at most the CUs, and for narrow products of up to 128 rows
+// that 128 x 128 tiles leave mostly idle; 256 x 256 tiles for the rest and for
+// long prefill chunks.
+// Cache-cold, us as 128 x 128 / 256 x 128 / 256 x 256 tiles (the last two with
+// their last round cut where that applies).  Wide products: 8B gate/up at M =
+// 128 48.4 / 58.1 / 58.3, 192 68.9 / 60.5 / 63.7, 256 76.9 / 66.8 / 74.7, 301 97.0
+// / 95.1 / 73.1; 70B gate/up at M = 128 181.8 / 168.0 / 170.3, 200 263 / 238 / 191;
+// a head of 32000 at M = 128 51.9 / 74.6 / 75.5, 192 73.4 / 67.5 / 78.5; of 128256
+// at M = 128 233.9 / 220.3 / 224.2, 192 299 / 286 / 238.  Narrow products: O at M =
+// 1000 40.9 / 44.7 / 50.9, 1100 52.1 / 65.4 / 55.6; QKV at M = 1000 66.5 / 54.4 /
+// 60.6, 1100 64.7 / 54.1 / 63.1.  kMidMaxRows suits O; with the longer K of 8B
+// down 256 x 256 tiles and a cut last round are ahead from about 600 rows (117.7 /
+// 104.8 / 81.6; at 1000 130 / 114 / 104), as for 70B QKV from 160 (66.4 / 63.5 /
+// 49.9), which the rule does not use.
 GemmPlan plan_gemm(int M, int N, int Kp, int epilogue, int64_t part_cap) {
   GemmPlan p{GemmKind::kBig, 4, 1, 1, 0};
   const bool can_split = part_cap > 0;
@@ -914,9 +922,8 @@ GemmPlan plan_gemm(int M, int N, int Kp, int epilogue, int64_t part_cap) {
   if (split) p.ks = tiled_k_splits(kind_tiles, cus, M, Kp);
   // Narrow products of up to 128 rows whose 128 x 128 tiles fill under three
   // quarters of the CUs even with k slices take 256 x 128 tiles when those
-  // reach at least as many workgroups (70B QKV at M=128: 40 tiles x 4 slices,
-  // 55 us, against 80 x 2 of 128 x 128, 63 us, in a probe; larger batches
-  // were not measured with this rule and keep 128 x 128 tiles).
+  // reach at least as many workgroups (70B QKV at M=128: 40 tiles x 4 slices
+  // 46.9 us, 80 x 2 of 128 x 128 47.8; at M=80 42.1 against 43.1).
   if (split && p.kind == GemmKind::kMid && M <= WideTile::BM && 4 * mid_tiles * p.ks < 3 * cus) {
     const int wks = tiled_k_splits(wide_tiles, cus, M, Kp);
     if (wide_tiles * wks >= mid_tiles * p.ks) {
