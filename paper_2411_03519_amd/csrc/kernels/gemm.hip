@@ -62,41 +62,52 @@ __device__ __forceinline__ void store_swiglu(f32x4 gt, f32x4 up, int m, int j, u
 // KS > 1 the slice sums go to part[slice][m][n] and the consumer kernel adds
 // the slices (in slice order) where it reads the result.
 // ---------------------------------------------------------------------------
-// q / k / v of one row for dims d0 .. d0+3 (a) and d0+half .. (b) of a head
-// whose features start at column f0 of the QKV product
-__device__ __forceinline__ void store_rope_kv(f32x4 a, f32x4 b, int m, int head, int d0, const RopeKV& rk) {
+// Where the QKV epilogue stores one row: its q, its KV page and its key there.
+struct RowOut {
+  uint16_t *q, *page;
+  int key;
+};
+__device__ __forceinline__ RowOut row_out(int m, int slot, const RopeKV& rk) {
+  return {rk.q + static_cast<size_t>(m) * (rk.nq * rk.hd), rk.kv + kv_offset(slot / kPage, 0, rk.nkv, 0, 0, rk.hd, 0),
+          slot % kPage};
+}
+
+// q / k / v of one row for dims d0 .. d0+3 (a; d0 % 4 == 0) and d0+half .. (b) of
+// a head; c: cos and sin of dims d0 .. d0+3 at its position (not read for v).
+// In a K tile the 4 dims are consecutive elements, in a V^T tile 16 bytes apart;
+// half (a multiple of 32) dims on is 16 * half elements on in both.
+__device__ __forceinline__ void store_rope_kv(f32x4 a, f32x4 b, const float4 (&c)[2], const RowOut& o, int head, int d0,
+                                              const RopeKV& rk) {
   const int hd = rk.hd, half = hd / 2;
-  const int sl = rk.slot[m], page = sl / kPage, off = sl % kPage;
   if (head < rk.nq + rk.nkv) {
-    const float2* c = rk.rope + static_cast<size_t>(rk.pos[m]) * half + d0;
+    const float cs[8] = {c[0].x, c[0].y, c[0].z, c[0].w, c[1].x, c[1].y, c[1].z, c[1].w};
     f32x4 ra, rb;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float2 cs = c[i];
-      ra[i] = a[i] * cs.x - b[i] * cs.y;
-      rb[i] = a[i] * cs.y + b[i] * cs.x;
+      // (which product is rounded is fixed, so that every kernel gives the same bits)
+      ra[i] = fmaf(a[i], cs[2 * i], -(b[i] * cs[2 * i + 1]));
+      rb[i] = fmaf(b[i], cs[2 * i], a[i] * cs[2 * i + 1]);
     }
-    if (head < rk.nq) {
-      uint16_t* dst = rk.q + (static_cast<size_t>(m) * rk.nq + head) * hd;
-      *reinterpret_cast<uint2*>(dst + d0) = make_uint2(pack_bf16x2(ra[0], ra[1]), pack_bf16x2(ra[2], ra[3]));
-      *reinterpret_cast<uint2*>(dst + d0 + half) = make_uint2(pack_bf16x2(rb[0], rb[1]), pack_bf16x2(rb[2], rb[3]));
-    } else {
-      // dims d0 .. d0+3 (d0 % 4 == 0) are 4 consecutive elements of the K
-      // tile: one 8-byte store each for the two halves
-      uint16_t* kt = rk.kv + kv_offset(page, 0, rk.nkv, head - rk.nq, 0, hd, 0);
-      *reinterpret_cast<uint2*>(kt + k_tile_offset(off, d0)) =
-          make_uint2(pack_bf16x2(ra[0], ra[1]), pack_bf16x2(ra[2], ra[3]));
-      *reinterpret_cast<uint2*>(kt + k_tile_offset(off, d0 + half)) =
-          make_uint2(pack_bf16x2(rb[0], rb[1]), pack_bf16x2(rb[2], rb[3]));
-    }
+    const bool q = head < rk.nq;
+    uint16_t* dst = q ? o.q + head * hd + d0 : o.page + (head - rk.nq) * (kPage * hd) + k_tile_offset(o.key, d0);
+    *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16x2(ra[0], ra[1]), pack_bf16x2(ra[2], ra[3]));
+    *reinterpret_cast<uint2*>(dst + (q ? half : 16 * half)) =
+        make_uint2(pack_bf16x2(rb[0], rb[1]), pack_bf16x2(rb[2], rb[3]));
   } else {
-    uint16_t* vt = rk.kv + kv_offset(page, 1, rk.nkv, head - rk.nq - rk.nkv, 0, hd, 0);
+    uint16_t* dst = o.page + (head - rk.nq) * (kPage * hd) + vt_tile_offset(d0, o.key);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      vt[vt_tile_offset(d0 + i, off)] = f32_to_bf16(a[i]);
-      vt[vt_tile_offset(d0 + i + half, off)] = f32_to_bf16(b[i]);
+      dst[8 * i] = f32_to_bf16(a[i]);
+      dst[16 * half + 8 * i] = f32_to_bf16(b[i]);
     }
   }
+}
+
+// cos and sin of dims d0 .. d0+3 (d0 % 4 == 0) at a position
+__device__ __forceinline__ void load_rope(float4 (&c)[2], int pos, int d0, const RopeKV& rk) {
+  const float4* p = reinterpret_cast<const float4*>(rk.rope + static_cast<size_t>(pos) * (rk.hd / 2) + d0);
+  c[0] = p[0];
+  c[1] = p[1];
 }
 
 template <int MT, int NT, int EPI, int PF, int NW>
@@ -214,8 +225,12 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const uint16_t* __
       }
       const int nt = t / MT, mt = t % MT;
       const int m = mt * 16 + m_lane;
-      const int f0 = n0 + nt * 16;
-      if (lane < 32 && m < M) store_rope_kv(a, b, m, f0 / rk.hd, 8 * ((f0 % rk.hd) / 16) + n_lane, rk);
+      const int f0 = n0 + nt * 16, head = f0 / rk.hd, d0 = 8 * ((f0 % rk.hd) / 16) + n_lane;
+      if (lane < 32 && m < M) {
+        float4 c[2];
+        if (head < rk.nq + rk.nkv) load_rope(c, rk.pos[m], d0, rk);
+        store_rope_kv(a, b, c, row_out(m, rk.slot[m], rk), head, d0, rk);
+      }
     }
   } else {
     for (int t = wave; t < NT * MT; t += NW) {
@@ -532,6 +547,53 @@ __device__ __forceinline__ void tile_epilogue_swiglu(const f32x4 (&acc)[S::TN][S
   }
 }
 
+// RoPE and the KV cache write.  A 16-row block of W holds 8 dims of a head's
+// first half, then the matching 8 of its second half (rotate-half interleave),
+// so two neighbouring blocks, which are of one head, are paired like gate and up.
+// A wave has nobody to cover its waits here, and each pair's rotation hangs on two
+// dependent loads (position, cos and sin): all slots and positions are loaded at
+// once, and the cos and sin of 16 rows while the 16 before them are stored.
+template <class S>
+__device__ __forceinline__ void tile_epilogue_rope_kv(const f32x4 (&acc)[S::TN][S::TM], int mw, int nw, int lane, int M,
+                                                      int N, const RopeKV& rk) {
+  constexpr int TM = S::TM, NP = S::TN / 2;
+  const int r16 = lane & 15, g = lane >> 4;
+  int slot[TM], pos[TM];
+#pragma unroll
+  for (int j = 0; j < TM; ++j) {
+    const int m = min(mw + 16 * j + r16, M - 1);
+    slot[j] = rk.slot[m];
+    pos[j] = rk.pos[m];
+  }
+  float4 c[2][NP][2];
+  // pair p: its head, and this lane's first dim
+  const int shift = 31 - __builtin_clz(rk.hd);  // (head dims are powers of two)
+  auto head = [&](int p) __attribute__((always_inline)) { return (nw + 32 * p) >> shift; };
+  auto dim = [&](int p) __attribute__((always_inline)) {
+    return 8 * (((nw + 32 * p) & (rk.hd - 1)) / 16 + (g >> 1)) + 4 * (g & 1);
+  };
+  auto load = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      if (nw + 32 * p < N && head(p) < rk.nq + rk.nkv) load_rope(c[j & 1][p], pos[j], dim(p), rk);
+  };
+  load(0);
+#pragma unroll
+  for (int j = 0; j < TM; ++j) {
+    if (j + 1 < TM) load(j + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    const int m = mw + 16 * j + r16;
+    const RowOut o = row_out(m, slot[j], rk);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      f32x4 x, y;
+      pair_halves(acc[2 * p][j], acc[2 * p + 1][j], x, y);
+      if (m < M && nw + 32 * p < N) store_rope_kv(x, y, c[j & 1][p], o, head(p), dim(p), rk);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // index of the direct load that rides behind MFMA u of nm (nd of them spread
 // evenly behind odd MFMAs), nd if none
 constexpr int load_behind(int u, int nm, int nd) {
@@ -705,20 +767,7 @@ __global__ __launch_bounds__(S::NTH, S::OCC) void gemm_tiled_kernel(const uint16
   const int mw = m0 + wm * TM * 16, nw = n0 + wn * TN * 16;
   uint4* const buf = lds + wave * (S::kLds / 4);
   if constexpr (EPI == kEpiRopeKV) {  // launched without k slices
-#pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      const int m = mw + 16 * j + r16;
-#pragma unroll
-      for (int i = 0; i < TN; i += 2) {
-        // a 16-row block of W: 8 dims of a head's first half, then the
-        // matching 8 of its second half (rotate-half interleave)
-        f32x4 x, y;
-        pair_halves(acc[i][j], acc[i + 1][j], x, y);
-        const int r0 = nw + 16 * (i + (g >> 1));
-        if (m < M && r0 < N) store_rope_kv(x, y, m, r0 / rk.hd, 8 * ((r0 % rk.hd) / 16) + 4 * (g & 1), rk);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+    tile_epilogue_rope_kv<S>(acc, mw, nw, lane, M, N, rk);
   } else if constexpr (EPI == kEpiSwiGLU) {
     if (KS > 1)
       tile_epilogue_f32<S, kEpiStoreF32>(acc, buf, mw, nw, m0, n0, lane, M, N, KS, slice, unit, outf, ldo, part);
@@ -1106,7 +1155,7 @@ hipError_t launch_gemm_rope_kv(const uint16_t* X, int ldx, const uint16_t* W, in
                                hipStream_t s) {
   if (M <= 0) return hipSuccess;
   if ((M > kRopeKVMaxRows && !gemm_rope_kv_fused(M, N, Kp, 0)) || N != (rk.nq + 2 * rk.nkv) * rk.hd || rk.hd % 32 ||
-      N % 32)
+      (rk.hd & (rk.hd - 1)) || N % 32)
     return hipErrorInvalidValue;
   if (M > kRopeKVMaxRows) {  // 256 x 256 tiles over all of K (no workspace: no split of the last round)
     even_rows<BigTile, 5>(M, [&](auto tm) {

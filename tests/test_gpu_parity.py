@@ -217,6 +217,29 @@ def test_one_token_items_match_decode_steps(metro, only_single):
         assert (got[keep] - want).abs().max().item() <= 2e-2
 
 
+@pytest.mark.parametrize("d,nq,nkv,hd,T", [(128, 2, 1, 64, 1001), (256, 4, 2, 64, 1279), (256, 2, 1, 128, 1300),
+                                           (512, 8, 8, 64, 2049), (512, 4, 4, 128, 1025)])
+def test_fused_rope_prefill_matches_short_chunks(metro, d, nq, nkv, hd, T):
+    """More than 1000 rows write q, K and V in the QKV product's epilogue, whose
+    waves may cover q, k and v heads at once; chunks of 300 rows go through the
+    RoPE kernel.  Both leave the same cache: the logits of the last token and
+    of a decode step agree up to fp32 rounding (bounded as the oracle's)."""
+    shape = dict(synth.TINY, d_model=d, n_heads=nq, n_kv_heads=nkv, head_dim=hd)
+    w = synth.llama_weights(shape, 5)
+    rng = np.random.default_rng(T)
+    toks = rng.integers(0, shape["vocab"], T)
+    with make_model(metro, shape, w, max_batch=8, max_tokens=4096, max_context=4096, max_seqs=8) as m:
+        out = torch.empty(4, 1, m.vocab, device="cuda")
+        one, parts = m.seq_open(), m.seq_open()
+        m.prefill_chunk([one], [toks], out[0])
+        for t in range(0, T, 300):
+            m.prefill_chunk([parts], [toks[t:t + 300]], out[1])
+        for s, o in ((one, out[2]), (parts, out[3])):
+            m.decode_step([s], np.array([7], np.int32), o)
+        assert (out[0] - out[1]).abs().max().item() <= 2e-2
+        assert (out[2] - out[3]).abs().max().item() <= 2e-2
+
+
 @pytest.mark.parametrize("d,vocab,launches", [(1024, 1024, 1), (1024, 4096, 1), (2048, 4096, 1), (4096, 1024, 2),
                                               (4096, 4096, 2)])
 def test_head_of_a_small_vocabulary(metro, d, vocab, launches):
