@@ -965,6 +965,18 @@ GemmPlan plan_gemm(int M, int N, int Kp, int epilogue, int64_t part_cap) {
   } else {
     p.kind = M <= kMidMaxRows ? GemmKind::kMid : GemmKind::kBig;
   }
+  // SwiGLU of a short K: most of a 256 x 256 tile's time is then its epilogue
+  // (expf and a division per output), one wave per SIMD, where two 128 x 128
+  // workgroups per CU cover each other.  Us, former 8-wave kernel / 256 x 256 /
+  // 128 x 128 tiles: K 128, N 1376, M 2000 12.5 / 15.8 / 9.1; K 256, N 5632, M 4000
+  // 40.6 / 43.6 / 24.6; K 768, N 2816, M 4000 26.7 / 28.2 / 22.3; from K 1024 on
+  // 256 x 256 tiles are no slower than that kernel, and ahead where N is wide
+  // (N 11264, M 1100 36.4 / 29.5 / 32.4).
+  if (p.kind == GemmKind::kBig && epilogue == kEpiSwiGLU && Kp <= 768) p.kind = GemmKind::kMid;
+  // Products narrower than a 256-row tile, of which much would be absent rows of
+  // W (former kernel / 256 x 256: K 384, N 32, M 2001 13.0 / 17.4 us; 256 x 128, M
+  // 128 8.4 / 10.2).
+  if (p.kind == GemmKind::kBig && N < BigTile::BN) p.kind = GemmKind::kMid;
   const int kind_tiles = p.kind == GemmKind::kMid    ? mid_tiles
                          : p.kind == GemmKind::kWide ? wide_tiles
                                                      : tiles_of(BigTile::BN, BigTile::BM);
@@ -973,7 +985,8 @@ GemmPlan plan_gemm(int M, int N, int Kp, int epilogue, int64_t part_cap) {
   // quarters of the CUs even with k slices take 256 x 128 tiles when those
   // reach at least as many workgroups (70B QKV at M=128: 40 tiles x 4 slices
   // 46.9 us, 80 x 2 of 128 x 128 47.8; at M=80 42.1 against 43.1).
-  if (split && p.kind == GemmKind::kMid && M <= WideTile::BM && 4 * mid_tiles * p.ks < 3 * cus) {
+  if (split && p.kind == GemmKind::kMid && M <= WideTile::BM && N >= WideTile::BN &&
+      4 * mid_tiles * p.ks < 3 * cus) {
     const int wks = tiled_k_splits(wide_tiles, cus, M, Kp);
     if (wide_tiles * wks >= mid_tiles * p.ks) {
       p.kind = GemmKind::kWide;

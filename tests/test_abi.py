@@ -86,6 +86,10 @@ PLAN_CASES = [
     (600, 4096, 14336, 1, True, "tile128x128", 1, 1),  # 8B down at an agent-trace batch
     (5376, 4096, 14336, 1, True, "tile256x256", 1, 2),  # 336 tiles: last 80 cut in 2 k slices
     (5376, 4096, 14336, 1, False, "tile256x256", 1, 1),
+    (2000, 1376, 768, 2, True, "tile128x128", 1, 1),    # SwiGLU of a short K
+    (2000, 1376, 896, 2, True, "tile256x256", 1, 1),
+    (2000, 1376, 768, 0, False, "tile256x256", 1, 1),
+    (2000, 224, 4096, 0, False, "tile128x128", 1, 1),   # narrower than a 256 x 256 tile
     (12800, 28672, 4096, 2, True, "tile256x256", 1, 1), # last round 224 of 256 CUs: no split
 ]
 

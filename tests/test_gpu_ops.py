@@ -131,8 +131,8 @@ def test_gemm_f32_epilogues(metro, M, K, N, epi, split):
 @pytest.mark.parametrize("M,K,F", [(3, 256, 688), (25, 256, 48), (64, 512, 112), (96, 256, 688), (130, 384, 80),
                                    (150, 128, 8192), (25, 128, 14336), (40, 128, 14336), (300, 128, 14336),
                                    (100, 256, 14336), (180, 128, 16384),
-                                   (300, 256, 8192),     # 128 tiles of 256 x 256: with a workspace 2 k slices each
-                                   (1300, 256, 2048),    # 96 ragged tiles: with a workspace 2 k slices each
+                                   (300, 256, 8192),     # K too short for 256 x 256 tiles: 128 x 128
+                                   (1300, 256, 2048),
                                    (90, 128, 28672),     # 224 tiles of 256 x 128 (70B gate/up-sized)
                                    (200, 256, 14336)])   # 224 tiles of 256 x 128 over two row blocks
 @pytest.mark.parametrize("split", [False, True])
@@ -299,17 +299,18 @@ def check_product(metro, M, N, K, epi, workspaces):
 # Row blocks of the tiled kernel: 64 rows for 33 to 64 rows, where the tiles are
 # enough; above, evened out over the rows (32 TM rows, TM 3 or 4 for 128-row
 # blocks, 5 .. 8 for 256-row ones).  Both sides of each step, with a last block
-# that is nearly empty and ragged N.  K = 384 is too short for k slices.
+# that is nearly empty and ragged N.  K is too short for k slices, and long enough
+# for SwiGLU to take 256 x 256 tiles.
 EVEN_ROWS = [(32, 16384), (33, 16384), (33, 17408), (48, 11008), (48, 16672), (64, 28672), (64, 1056), (96, 1056),
              (97, 1056), (192, 160), (193, 16384), (192, 28672), (257, 16416), (320, 16384), (321, 16384),
-             (385, 16384), (449, 16384), (513, 16384), (1001, 288), (1025, 288), (1281, 160)]
+             (385, 16384), (449, 16384), (513, 16384), (1001, 288), (1025, 288), (1281, 160), (1281, 416), (2001, 32)]
 
 
 @pytest.mark.parametrize("M,N", EVEN_ROWS)
 @pytest.mark.parametrize("epi", [0, 1, 2])
 def test_gemm_even_row_blocks(metro, M, N, epi):
     print(f"even rows M={M} N={N} epi={epi}", flush=True)
-    check_product(metro, M, N, 384, epi, (False, True))
+    check_product(metro, M, N, 896 if epi == 2 else 384, epi, (False, True))
 
 
 # The same blocks with k slices, or a last round cut into them: M, N, K,
@@ -327,9 +328,9 @@ SPLIT_BLOCKS = [(33, 4000, 2048, 0, "tile128x64", 8, 1),      # 64 rows, ragged 
                 (300, 16384, 4096, 0, "tile256x256", 2, 1),   # 2 x 160
                 (300, 16384, 1024, 2, "tile256x256", 1, 2),
                 (384, 16384, 4096, 1, "tile256x256", 2, 1),   # 2 x 192
-                (576, 28672, 512, 2, "tile256x256", 1, 2),    # 3 x 192 (8B gate/up)
+                (576, 28672, 1024, 2, "tile256x256", 1, 2),   # 3 x 192 (8B gate/up)
                 (440, 16384, 4096, 0, "tile256x256", 2, 1),   # 2 x 224
-                (660, 28672, 512, 2, "tile256x256", 1, 2),    # 3 x 224
+                (660, 28672, 1024, 2, "tile256x256", 1, 2),   # 3 x 224
                 (660, 28640, 512, 1, "tile256x256", 1, 2)]
 
 
