@@ -553,6 +553,9 @@ __device__ __forceinline__ void tile_epilogue_swiglu(const f32x4 (&acc)[S::TN][S
 // A wave has nobody to cover its waits here, and each pair's rotation hangs on two
 // dependent loads (position, cos and sin): all slots and positions are loaded at
 // once, and the cos and sin of 16 rows while the 16 before them are stored.
+// (One pair at a time, loads and all, before -> now, us of the whole product at
+// 2000 rows: K 256, N 512 33.6 -> 25.6; K 1024, N 1536 54.9 -> 39.6; K 4096, N
+// 6144 107 -> 95.)
 template <class S>
 __device__ __forceinline__ void tile_epilogue_rope_kv(const f32x4 (&acc)[S::TN][S::TM], int mw, int nw, int lane, int M,
                                                       int N, const RopeKV& rk) {
